@@ -4,10 +4,11 @@
 //  1. validate the sites and give each a 30-bit Hilbert key;
 //  2. radix-sort the sites into Hilbert order (internal order);
 //  3. bucket the sites into a uniform grid (stable radix sort by bucket);
-//  4. per site, clip the box by the bisector half-spaces of nearby sites,
-//     taken nearest-first from rings of buckets, until no farther site can
-//     cut the cell (its distance exceeds twice the largest vertex radius);
-//     the planes left bounding the cell are its neighbours (Sect. 2.1);
+//  4. per site, clip the box by the bisector half-spaces of nearby sites --
+//     its neighbours in Hilbert order first, then every other site nearer
+//     than twice the cell's largest vertex radius, found through a tree of
+//     bounding boxes over that order; the planes left bounding the cell are
+//     its neighbours (Sect. 2.1);
 //  5. make the lists symmetric, sort each row, and lay out the trace
 //     records (FP64 sites and FP32 offsets per neighbour, CSR by cell).
 #include <chrono>
@@ -41,20 +42,54 @@ __global__ void k_validate_keys(const double *__restrict__ sites, int64_t M, Box
     vals[i] = (int32_t)i;
 }
 
-__global__ void k_gather_sites(const double *__restrict__ sites, const int32_t *__restrict__ order, int64_t M,
-                               Site *__restrict__ out, int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm)
+// The sites in Hilbert order, and the boxes of their runs of kLeaf (level 0
+// of the box tree; the grid covers whole runs).
+__global__ void __launch_bounds__(256) k_gather_sites(const double *__restrict__ sites,
+                                                      const int32_t *__restrict__ order, int64_t M,
+                                                      Site *__restrict__ out, int32_t *__restrict__ perm,
+                                                      int32_t *__restrict__ inv_perm, Box6 *__restrict__ leaf)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    int32_t u = order[i];
-    Site s;
-    s.x = sites[3 * (int64_t)u];
-    s.y = sites[3 * (int64_t)u + 1];
-    s.z = sites[3 * (int64_t)u + 2];
-    s.uid = u;
-    out[i] = s;
-    perm[i] = u;
-    inv_perm[u] = (int32_t)i;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    Box6 b;
+    for (int a = 0; a < 3; ++a) {
+        b.lo[a] = __builtin_huge_val();
+        b.hi[a] = -__builtin_huge_val();
+    }
+    if (i < M) {
+        const int32_t u = order[i];
+        Site s;
+        s.x = b.lo[0] = b.hi[0] = sites[3 * (int64_t)u];
+        s.y = b.lo[1] = b.hi[1] = sites[3 * (int64_t)u + 1];
+        s.z = b.lo[2] = b.hi[2] = sites[3 * (int64_t)u + 2];
+        s.uid = u;
+        out[i] = s;
+        perm[i] = u;
+        inv_perm[u] = (int32_t)i;
+    }
+    for (int a = 0; a < 3; ++a)
+        for (int off = kLeaf / 2; off > 0; off >>= 1) {
+            b.lo[a] = fmin(b.lo[a], __shfl_xor(b.lo[a], off, 64));
+            b.hi[a] = fmax(b.hi[a], __shfl_xor(b.hi[a], off, 64));
+        }
+    if (i < M && i % kLeaf == 0) leaf[i / kLeaf] = b;
+}
+
+// A level of the box tree: box k covers the 64 boxes [64 k, 64 k + 64) below
+// (one wave each).
+__global__ void __launch_bounds__(64) k_box_level(const Box6 *__restrict__ below, int64_t n, Box6 *__restrict__ out)
+{
+    const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    Box6 b;
+    for (int a = 0; a < 3; ++a) {
+        b.lo[a] = __builtin_huge_val();
+        b.hi[a] = -__builtin_huge_val();
+    }
+    if (i < n) b = below[i];
+    for (int a = 0; a < 3; ++a) {
+        b.lo[a] = wave_min_f64(b.lo[a]);
+        b.hi[a] = wave_max_f64(b.hi[a]);
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = b;
 }
 
 struct GridArg {
@@ -91,7 +126,7 @@ __global__ void k_bucket_fill(const Site *__restrict__ sites, const int32_t *__r
 
 struct ClipArgs {
     const Site *sites;        // internal order
-    BucketGridView grid;
+    BoxTree tree;
     BoxArg box;
     int64_t M;
     int32_t *nbr;             // [M * kMaxNbr] first-pass lists
@@ -99,58 +134,81 @@ struct ClipArgs {
     uint8_t *walls;           // [M]
     int32_t *retry;           // [M] sites whose cell needs the large capacity
     int32_t *n_retry;
+    int32_t *touched;         // [M] sites whose cell asks for the strict order
+    int32_t *n_touched;
     int *err;
     double *volume;           // [M] cell volumes
     double *bbox;             // [6 M] cell bounding boxes, or null
 };
 
-// First pass: one wave per site with a small cell in LDS; cells that run
-// out of faces are queued for the second pass.
+// The result of the clipped cell i (n faces, or -ERR_*), by one lane.
+__device__ __forceinline__ void clip_result(const ClipArgs &A, int64_t i, int n, uint32_t walls, double vol)
+{
+    A.volume[i] = vol;
+    if (n == -ERR_CAPACITY) {
+        A.retry[atomicAdd(A.n_retry, 1)] = (int32_t)i;
+        n = 0;
+    } else if (n == -ERR_TOUCH) {
+        A.touched[atomicAdd(A.n_touched, 1)] = (int32_t)i;
+        n = 0;
+    } else if (n < 0) {
+        atomicOr(A.err, -n);
+        n = 0;
+    }
+    A.cnt[i] = n;
+    A.walls[i] = (uint8_t)walls;
+}
+
+// First pass: one wave per site with a small cell; cells that run out of
+// vertices are queued for the large capacity, cells in which a cut passed
+// through a vertex (lattices) for the strict order. The grid is a multiple
+// of kXcds blocks: block b runs on XCD b mod kXcds, and each XCD takes one
+// contiguous part of the Hilbert order, so that its L2 holds the sites
+// around it.
+constexpr int kXcds = 8;
 __global__ void __launch_bounds__(64) k_clip(ClipArgs A)
 {
     __shared__ WaveCellSmall cell;
-    const int64_t i = blockIdx.x;
-    uint8_t wm = 0;
-    double vol = 0.0, bb[6];
-    int n = wclip_site(cell, A.sites, A.grid, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr, &wm, &vol,
-                       A.bbox ? bb : nullptr);
-    if (threadIdx.x == 0) {
-        A.volume[i] = vol;
-        if (A.bbox && n >= 0)
-            for (int a = 0; a < 6; ++a) A.bbox[6 * i + a] = bb[a];
-        if (n == -ERR_CAPACITY) {
-            A.retry[atomicAdd(A.n_retry, 1)] = (int32_t)i;
-            n = 0;
-        } else if (n < 0) {
-            atomicOr(A.err, -n);
-            n = 0;
-        }
-        A.cnt[i] = n;
-        A.walls[i] = wm;
-    }
+    const int64_t i = (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+    if (i >= A.M) return;
+    uint32_t walls = 0;
+    double vol = 0.0;
+    const int n = wclip_site<WaveCellSmall, false>(cell, A.sites, A.M, A.tree, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr,
+                                                   walls, vol, A.bbox ? A.bbox + 6 * i : nullptr);
+    if (threadIdx.x == 0) clip_result(A, i, n, walls, vol);
 }
 
-// Second pass over the queued sites, with large cells (up to 255 faces).
+// The queued cells again, in the strict order.
+__global__ void __launch_bounds__(64) k_clip_strict(ClipArgs A)
+{
+    __shared__ WaveCellSmall cell;
+    const int64_t i = A.touched[blockIdx.x];
+    uint32_t walls = 0;
+    double vol = 0.0;
+    const int n = wclip_site<WaveCellSmall, true>(cell, A.sites, A.M, A.tree, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr,
+                                                  walls, vol, A.bbox ? A.bbox + 6 * i : nullptr);
+    if (threadIdx.x == 0) clip_result(A, i, n, walls, vol);
+}
+
+// The queued sites with large cells (up to 255 planes).
 __global__ void __launch_bounds__(64) k_clip_big(ClipArgs A, int32_t *__restrict__ big_nbr, int32_t *__restrict__ slot)
 {
     __shared__ WaveCellBig cell;
     const int k = blockIdx.x;
     const int64_t i = A.retry[k];
-    uint8_t wm = 0;
-    double vol = 0.0, bb[6];
-    int n = wclip_site(cell, A.sites, A.grid, A.box, i, big_nbr + (int64_t)k * kMaxNbrBig, kMaxNbrBig, &wm, &vol,
-                       A.bbox ? bb : nullptr);
+    uint32_t wm = 0;
+    double vol = 0.0;
+    int n = wclip_site<WaveCellBig, true>(cell, A.sites, A.M, A.tree, A.box, i, big_nbr + (int64_t)k * kMaxNbrBig,
+                                          kMaxNbrBig, wm, vol, A.bbox ? A.bbox + 6 * i : nullptr);
     if (threadIdx.x == 0) {
         A.volume[i] = vol;
-        if (A.bbox && n >= 0)
-            for (int a = 0; a < 6; ++a) A.bbox[6 * i + a] = bb[a];
         slot[i] = k;
         if (n < 0) {
             atomicOr(A.err, -n);
             n = 0;
         }
         A.cnt[i] = n;
-        A.walls[i] = wm;
+        A.walls[i] = (uint8_t)wm;
     }
 }
 
@@ -604,6 +662,13 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     int32_t *extra = dalloc<int32_t>(M, rc, tmp, A);
     int32_t *total = dalloc<int32_t>(M, rc, tmp, A);
     int32_t *start = dalloc<int32_t>(M + 1, rc, tmp, A);
+    BoxTree tree;   // boxes over runs of kLeaf sites, then over 64 boxes each
+    Box6 *boxes[3];
+    for (int v = 0; v < 3; ++v) {
+        const int64_t per = v == 0 ? kLeaf : 64, below = v == 0 ? M : tree.n[v - 1];
+        tree.n[v] = (below + per - 1) / per;
+        tree.level[v] = boxes[v] = dalloc<Box6>(tree.n[v], rc, tmp, A);
+    }
     int *hdr = nullptr;
 
     auto fail = [&](vor_status s) {
@@ -627,7 +692,10 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     rc = vrt_radix_sort_pairs(keys, vals, keys2, vals2, M, 3 * kHilbertBits, hist, hist_len, st);
     if (rc != VOR_OK) return fail(rc);
     hipLaunchKernelGGL(k_gather_sites, dim3(blocks_for(M, T)), dim3(T), 0, st, sites, vals, M, g.sites, g.perm,
-                       g.inv_perm);
+                       g.inv_perm, boxes[0]);
+    for (int v = 1; v < 3; ++v)
+        hipLaunchKernelGGL(k_box_level, dim3((unsigned)tree.n[v]), dim3(64), 0, st, boxes[v - 1], tree.n[v - 1],
+                           boxes[v]);
 
     // bucket the Hilbert-ordered sites (stable: within a bucket, Hilbert order)
     GridArg ga;
@@ -649,7 +717,7 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     // clip every cell: small cells first, the overflowing ones again with large cells
     ClipArgs ca;
     ca.sites = g.sites;
-    ca.grid = bucket_view(g);
+    ca.tree = tree;
     ca.box = ba;
     ca.M = M;
     ca.nbr = nbr0;
@@ -657,11 +725,13 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     ca.walls = g.wall_mask;
     ca.retry = retry;
     ca.n_retry = err + 2;
+    ca.touched = extra;   // filled again for the rows
+    ca.n_touched = err + 3;
     ca.err = err;
     ca.volume = g.volume;
     ca.bbox = g.bbox;
     if (hipMemsetAsync(slot, 0xff, sizeof(int32_t) * M, st) != hipSuccess) return fail(VOR_EDEVICE);
-    hipLaunchKernelGGL(k_clip, dim3((unsigned)M), dim3(64), 0, st, ca);
+    hipLaunchKernelGGL(k_clip, dim3((unsigned)(kXcds * ((M + kXcds - 1) / kXcds))), dim3(64), 0, st, ca);
     if (hipGetLastError() != hipSuccess) return fail(VOR_EDEVICE);
     int hflags[4] = {0, 0, 0, 0};
     if (hipMemcpyAsync(hflags, err, 4 * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -669,6 +739,14 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         return fail(VOR_EDEVICE);
     if (hflags[0] & ERR_DUP) return fail(VOR_EDUP);
     if (hflags[0] & (ERR_CAPACITY | ERR_DEGENERATE)) return fail(VOR_ECAPACITY);
+    if (hflags[3] > 0) {
+        hipLaunchKernelGGL(k_clip_strict, dim3((unsigned)hflags[3]), dim3(64), 0, st, ca);
+        if (hipMemcpyAsync(hflags, err, 4 * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess)
+            return fail(VOR_EDEVICE);
+        if (hflags[0] & ERR_DUP) return fail(VOR_EDUP);
+        if (hflags[0] & (ERR_CAPACITY | ERR_DEGENERATE)) return fail(VOR_ECAPACITY);
+    }
     const int n_retry = hflags[2];
     int32_t *big_nbr = nullptr;
     if (n_retry > 0) {
