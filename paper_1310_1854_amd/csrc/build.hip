@@ -810,6 +810,7 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         nslots = ns;
     }
     if (nslots + kRecPad > 0x7fffffffLL) return fail(VOR_ECAPACITY);
+    g.nslots = nslots;
     g.rows = dalloc<int2>(M, rc, keep, A);
     g.rec64 = dalloc<Rec64>(g.nnz + kRecPad, rc, keep, A);
     g.blk = dalloc<Slot>(nslots + kRecPad, rc, keep, A);

@@ -41,6 +41,7 @@
 // cell in LDS, as before, took 137 and 38 ms.
 #pragma once
 
+#include "lanes.h"
 #include "vrt_internal.h"
 
 namespace vrt {
@@ -126,64 +127,6 @@ __device__ __forceinline__ void lds_order()
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-}
-
-__device__ __forceinline__ uint32_t lane_u32(uint32_t v, int l)
-{
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
-}
-
-__device__ __forceinline__ double lane_f64(double v, int l)
-{
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint64_t r = (uint64_t)lane_u32((uint32_t)u, l) | ((uint64_t)lane_u32((uint32_t)(u >> 32), l) << 32);
-    return __longlong_as_double((long long)r);
-}
-
-__device__ __forceinline__ float lane_f32(float v, int l) { return __uint_as_float(lane_u32(__float_as_uint(v), l)); }
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
-}
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v)
-{
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint64_t r = (uint64_t)dpp_u32<CTRL>((uint32_t)u) | ((uint64_t)dpp_u32<CTRL>((uint32_t)(u >> 32)) << 32);
-    return __longlong_as_double((long long)r);
-}
-
-// Minimum and maximum over the wave (row shifts, then row broadcasts; lanes
-// without a source keep their own value; the result is lane 63's).
-#define VRT_WAVE_REDUCE(v, op, dpp)  \
-    v = op(v, dpp<0x111>(v));        \
-    v = op(v, dpp<0x112>(v));        \
-    v = op(v, dpp<0x114>(v));        \
-    v = op(v, dpp<0x118>(v));        \
-    v = op(v, dpp<0x142>(v));        \
-    v = op(v, dpp<0x143>(v))
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
-{
-    VRT_WAVE_REDUCE(v, min, dpp_u32);
-    return lane_u32(v, 63);
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
-{
-    VRT_WAVE_REDUCE(v, max, dpp_u32);
-    return lane_u32(v, 63);
-}
-__device__ __forceinline__ double wave_min_f64(double v)
-{
-    VRT_WAVE_REDUCE(v, fmin, dpp_f64);
-    return lane_f64(v, 63);
-}
-__device__ __forceinline__ double wave_max_f64(double v)
-{
-    VRT_WAVE_REDUCE(v, fmax, dpp_f64);
-    return lane_f64(v, 63);
 }
 
 __device__ __forceinline__ uint64_t wave_or_u64(uint64_t v)

@@ -91,9 +91,11 @@ __device__ __forceinline__ int32_t nearest_in_blocks(const LocView &L, const dou
     return best_m;
 }
 
-// The same search by a whole wave for one point shared by its 64 lanes:
-// the lanes take the list in turn, then the best (distance, user index) is
-// reduced across the wave. Returns the internal index on every lane.
+// The same search by W lanes for one point that they share (a whole wave, or
+// an aligned group of 16): the lanes take the list in turn, then the best
+// (distance, user index) is reduced across them. Returns the internal index
+// on every lane.
+template <int W = 64>
 __device__ __forceinline__ int32_t nearest_in_blocks_wave(const LocView &L, const double q[3])
 {
     int b[3];
@@ -101,7 +103,7 @@ __device__ __forceinline__ int32_t nearest_in_blocks_wave(const LocView &L, cons
     const int64_t k = ((int64_t)b[0] * L.dims[1] + b[1]) * L.dims[2] + b[2];
     double best = __builtin_huge_val();
     int32_t best_u = 0x7fffffff, best_m = -1;
-    for (int s = L.start[k] + (int)(threadIdx.x & 63); s < L.start[k + 1]; s += 64) {
+    for (int s = L.start[k] + (int)(threadIdx.x & (W - 1)); s < L.start[k + 1]; s += W) {
         const int32_t m = L.cells[s];
         const Site p = L.sites[m];
         const double dx = q[0] - p.x, dy = q[1] - p.y, dz = q[2] - p.z;
@@ -113,7 +115,7 @@ __device__ __forceinline__ int32_t nearest_in_blocks_wave(const LocView &L, cons
             best_m = m;
         }
     }
-    for (int off = 32; off > 0; off >>= 1) {
+    for (int off = W / 2; off > 0; off >>= 1) {
         const double ob = __shfl_xor(best, off, 64);
         const int32_t ou = __shfl_xor(best_u, off, 64);
         const int32_t om = __shfl_xor(best_m, off, 64);
@@ -126,13 +128,14 @@ __device__ __forceinline__ int32_t nearest_in_blocks_wave(const LocView &L, cons
     return best_m;
 }
 
-// nearest_site for a point shared by the whole wave: the sites of each
-// bucket are split over the 64 lanes, and after each shell the lanes agree
+// nearest_site for a point that W lanes share: the sites of each bucket are
+// split over them, and after each shell the lanes agree
 // on the lexicographic minimum of (squared distance, user index). The
 // shells visited, the distances and the minimum are those of nearest_site.
+template <int W = 64>
 __device__ inline int32_t nearest_site_wave(const BucketGridView &g, const double q[3], int32_t *uid_out)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & (W - 1);
     int b[3];
     for (int a = 0; a < 3; ++a) b[a] = bucket_coord(q[a], g.lo[a], g.inv_h[a], g.dims[a]);
     double best = 1e308 * 10.0;
@@ -141,7 +144,7 @@ __device__ inline int32_t nearest_site_wave(const BucketGridView &g, const doubl
     for (int r = 0;; ++r) {
         for_shell(g, b, r, [&](int bk) {
             const int s0 = g.start[bk], s1 = g.start[bk + 1];
-            for (int s = s0 + lane; s < s1; s += 64) {
+            for (int s = s0 + lane; s < s1; s += W) {
                 const Site p = g.items[s];
                 const double dx = q[0] - p.x, dy = q[1] - p.y, dz = q[2] - p.z;
                 const double d = dx * dx + dy * dy + dz * dz;
@@ -154,7 +157,7 @@ __device__ inline int32_t nearest_site_wave(const BucketGridView &g, const doubl
                 }
             }
         });
-        for (int off = 32; off > 0; off >>= 1) {
+        for (int off = W / 2; off > 0; off >>= 1) {
             const double ob = __shfl_xor(best, off, 64);
             const int32_t ou = __shfl_xor(best_u, off, 64);
             const int32_t oi = __shfl_xor(best_i, off, 64);

@@ -9,8 +9,7 @@
 // ones.
 #include <mutex>
 
-#include "trace_core.h"
-#include "locate_core.h"
+#include "group_core.h"
 
 using namespace vrt;
 
@@ -35,6 +34,8 @@ struct TraceArgs {
     int64_t *work;        // [1] spill chunks asked for, [2] rays past their window, [kHead0 ..] work queues
     int32_t *start;       // start cell (internal) of every ray from k_start_cells, or null: located at ray start
     Extras X;             // interaction points and tallies (kernels with EXT only)
+    int32_t start_given;  // start holds the cells already
+    int32_t persistent;   // the caller asked for persistent waves, and with them for their counters
 };
 
 #ifndef VRT_REFILL_MIN
@@ -87,12 +88,11 @@ __device__ __forceinline__ void ray_window(const TraceArgs &A, int64_t ray, RayS
     }
 }
 
-// Results of a finished ray.
-template <bool SEGS, bool EXT, int MODE>
-__device__ __forceinline__ void ray_finish(const TraceArgs &A, int64_t ray, RayState &R, const RayStats &S)
+// Results of a finished ray whose segments are all written.
+template <bool SEGS, bool EXT>
+__device__ __forceinline__ void ray_results(const TraceArgs &A, int64_t ray, RayState &R, const RayStats &S)
 {
     if (EXT) ray_extras_finish(A.X, ray, R);
-    if (SEGS) finish_segments<cells_per_store<MODE, EXT>(), lens_per_store<MODE, EXT>()>(A.O, R, S.cnt);
     if (SEGS && S.cnt > R.cap) {
         if (A.work) atomicAdd((unsigned long long *)&A.work[2], 1ull);
         if (R.st == RAY_OK && (!A.O.spill_cell || R.chunk == -2)) R.st = RAY_OVERFLOW;
@@ -101,6 +101,14 @@ __device__ __forceinline__ void ray_finish(const TraceArgs &A, int64_t ray, RayS
     A.n_seg[ray] = S.cnt;
     if (A.status) A.status[ray] = R.st;
     if (A.n_fb) A.n_fb[ray] = S.nfb;
+}
+
+// A finished ray: the segments still held back, then its results.
+template <bool SEGS, bool EXT, int MODE>
+__device__ __forceinline__ void ray_finish(const TraceArgs &A, int64_t ray, RayState &R, const RayStats &S)
+{
+    if (SEGS) finish_segments<cells_per_store<MODE, EXT>(), lens_per_store<MODE, EXT>()>(A.O, R, S.cnt);
+    ray_results<SEGS, EXT>(A, ray, R, S);
 }
 
 __device__ __forceinline__ void flush_counters(const TraceArgs &A, const RayStats &S)
@@ -304,6 +312,77 @@ __global__ void __launch_bounds__(256) VRT_OCC k_trace_persistent(TraceArgs A)
     }
 }
 
+// One ray per group of kGroupLanes lanes (group_core.h), for launches too
+// small to fill the device: the start cell is found here too, by the group.
+// The waves of a block add up their counts in LDS and the last one passes
+// them on: atomics to the caller's counters all go to one line and take
+// turns (12 ns each measured), for longer than short paths take.
+constexpr int kGroupLanes = 16;
+template <int MODE, bool SEGS, bool EXT>
+__global__ void __launch_bounds__(256) k_trace_group(TraceArgs A)
+{
+    constexpr int W = kGroupLanes;
+    __shared__ unsigned long long sum[7];
+    __shared__ int ended;
+    if (threadIdx.x < 7) sum[threadIdx.x] = 0;
+    if (threadIdx.x == 7) ended = 0;
+    __syncthreads();
+    const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) / W;
+    const int li = threadIdx.x & (W - 1);
+    RayStats S;
+    if (q < A.N) {
+        const int64_t ray = A.order ? (int64_t)A.order[q] : q;
+        RayState R;
+        ray_window<SEGS>(A, ray, R);
+        R.tau = 0.0;
+        R.s_c = 0.0;
+        double s0;
+        R.st = ray_setup<EXT>(A.G, A.I, ray, R.r0, R.k, R.L, s0);
+        int32_t m = -1;
+        if (R.st == RAY_OK) {
+            if (A.start_given) {
+                m = A.start[ray];
+            } else {
+                double p[3];
+                start_point(R.r0, R.k, s0, p);
+                if (A.loc.start) m = nearest_in_blocks_wave<W>(A.loc, p);
+                if (m < 0) m = nearest_site_wave<W>(A.G.grid, p, nullptr);
+                if (A.start && li == 0) A.start[ray] = m;
+            }
+            R.s_c = s0;
+            group_walk<MODE, SEGS, EXT, false, W>(A.G, A.I, A.O, A.X, R, S, m);
+        } else {
+            R.L = 0.0;
+            if (EXT) ray_extras_begin(A.X, ray, R);
+            if (A.start && !A.start_given && li == 0) A.start[ray] = m;
+        }
+        if (li == 0) {
+            ray_results<SEGS, EXT>(A, ray, R, S);
+            atomicAdd(&sum[0], (unsigned long long)S.cnt);
+            if (S.nfb) atomicAdd(&sum[1], (unsigned long long)S.nfb);
+            if (S.nredo) atomicAdd(&sum[2], (unsigned long long)S.nredo);
+            atomicAdd(&sum[3], (unsigned long long)S.steps);
+            atomicAdd(&sum[4], (unsigned long long)S.recs);
+        }
+    }
+    if (!A.counters) return;
+    if (A.persistent) {   // a wave runs as long as its longest path
+        int it = S.steps;
+        for (int off = 32; off > 0; off >>= 1) it = max(it, __shfl_xor(it, off, 64));
+        if ((threadIdx.x & 63) == 0 && it > 0) {
+            atomicAdd(&sum[5], (unsigned long long)it);
+            atomicAdd(&sum[6], 1ull);
+        }
+    }
+    int at = 0;
+    if ((threadIdx.x & 63) == 0) at = __hip_atomic_fetch_add(&ended, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__shfl(at, 0, 64) == 3) {   // the block's last wave
+        const int i = threadIdx.x & 63;
+        const unsigned long long v = i < 7 ? __hip_atomic_load(&sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0ull;
+        if (v) atomicAdd(&A.counters[i], v);
+    }
+}
+
 // Sort keys of a ray: Hilbert index of its origin (10 bits per axis over the
 // box) and of its direction ((k/|k| + 1)/2 over the unit cube), and its
 // chord -- the distance to the wall it heads for (Eq. 5 on every axis) --
@@ -487,31 +566,48 @@ extern "C" vor_status vor_locate(const vor_grid *G, const double *pts, int64_t N
     return hipGetLastError() == hipSuccess ? VOR_OK : VOR_EDEVICE;
 }
 
-// Resident blocks per compute unit of a persistent trace kernel (a property
-// of the compiled kernel: queried once per process).
-template <int MODE, bool SEGS, bool EXT>
-int persistent_blocks_per_cu()
+// Resident blocks per compute unit of a kernel (a property of the compiled
+// kernel: queried once per process and kernel).
+template <class K>
+int resident_blocks_per_cu(K kernel)
 {
-    static const int per_cu = [] {
-        int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_trace_persistent<MODE, SEGS, EXT>, 256, 0) !=
-                hipSuccess ||
-            n < 1)
-            n = 1;
-        return n;
-    }();
-    return per_cu;
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 256, 0) != hipSuccess || n < 1) n = 1;
+    return n;
 }
 
-// Launch of the trace kernel: one ray per lane, or persistent waves (as
-// many blocks as fit on the device at once; cus = the grid's device's
-// compute units, read when the grid was built).
+// Up to how many rays a launch gives each ray a group of lanes. Kernel times
+// of one ray per lane / per group (us, whole paths into windows, mixed):
+//   rays                    61        1000       20000       40000       80000
+//   exp. disc, 10^5     478/187    956/321   1019/520   1045/861   1077/1438
+//   flared disc, 10^6  1109/369   1452/498   1812/881  2026/1356   1991/2077
+//   clumpy, 3x10^6     1418/448   1854/614  2124/1209  2052/2029   2309/3591
+// and without segments 2022/1491 and 2181/2562 on the last one at 40000 and
+// 80000; in FP64 2629/2005 and 3302/3512 (1437/827 and 1626/1385 on the
+// first), with transport outputs 2144/2786 and 2730/4913 (mixed).
+template <int MODE, bool SEGS, bool EXT>
+constexpr int64_t group_max_rays()
+{
+    return !EXT && (MODE == VOR_MODE_FP64 || !SEGS) ? 1 << 16 : 1 << 15;
+}
+
+// Launch of the trace kernel: one ray per group of lanes, or the start cells
+// and then one ray per lane or persistent waves (as many blocks as fit on the
+// device at once; cus = the grid's device's compute units, read when the
+// grid was built).
 template <int MODE, bool SEGS, bool EXT>
 vor_status launch_trace_ext(const TraceArgs &A, bool persistent, int cus, hipStream_t st)
 {
-    const int T = 256;
+    constexpr int T = 256;
+    if (A.N <= group_max_rays<MODE, SEGS, EXT>()) {
+        constexpr int rays = T / kGroupLanes;
+        hipLaunchKernelGGL((k_trace_group<MODE, SEGS, EXT>), dim3((unsigned)((A.N + rays - 1) / rays)), dim3(T), 0, st, A);
+        return VOR_OK;
+    }
+    if (A.start && !A.start_given)
+        hipLaunchKernelGGL(k_start_cells, dim3((unsigned)((A.N + T - 1) / T)), dim3(T), 0, st, A);
     if (persistent) {
-        const int per_cu = persistent_blocks_per_cu<MODE, SEGS, EXT>();
+        static const int per_cu = resident_blocks_per_cu(k_trace_persistent<MODE, SEGS, EXT>);
         const int64_t blocks = std::min<int64_t>((int64_t)cus * per_cu, (A.N + T - 1) / T);
         hipLaunchKernelGGL((k_trace_persistent<MODE, SEGS, EXT>), dim3((unsigned)std::max<int64_t>(blocks, 1)),
                            dim3(T), 0, st, A);
@@ -597,8 +693,8 @@ extern "C" vor_status vor_trace(const vor_grid *G, const double *origins, const 
     hipStream_t st = (hipStream_t)stream;
     const int T = 256;
     if (A.work) hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(64), 0, st, A.work, VOR_WORK_WORDS);
-    if (A.start && !(opts && opts->start_given))
-        hipLaunchKernelGGL(k_start_cells, dim3((unsigned)((N + T - 1) / T)), dim3(T), 0, st, A);
+    A.start_given = opts && opts->start_given;
+    A.persistent = persistent;
     if (spill) {
         int64_t nb = std::min<int64_t>((N + T - 1) / T, 65535);
         hipLaunchKernelGGL(k_fill_i64, dim3((unsigned)nb), dim3(T), 0, st, A.O.spill_first, N, (int64_t)-1);

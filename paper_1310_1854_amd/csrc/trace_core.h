@@ -25,6 +25,7 @@ struct GridRef {
     const int32_t *blk_off;  // where each cell's block starts when the grid keeps it (compact blocks; null: block_of)
     const Slot *blk64;       // FP64 cell blocks (header, FP64 neighbour sites, block offsets): FP64-mode steps
     const int32_t *blk64_off;
+    int32_t blk_slots, blk64_slots;   // slots of the two tables that may be read (the zeroed ones at the end included)
     const double *rho_int;   // the density bound to the grid, internal order
     BucketGridView grid;
     double lo[3], hi[3];
@@ -135,6 +136,8 @@ inline GridRef grid_ref(const Grid &g, int32_t max_steps, double eps_mix)
     G.blk_off = g.blk_off;
     G.blk64 = g.blk64;
     G.blk64_off = g.blk64_off;
+    G.blk_slots = (int32_t)(g.nslots + kRecPad);
+    G.blk64_slots = (int32_t)(g.nslots64 + kRecPad);
     G.rho_int = g.rho_int;
     G.grid = bucket_view(g);
     double diag = 0.0, cmax = 0.0;

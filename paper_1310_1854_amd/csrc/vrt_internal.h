@@ -112,6 +112,7 @@ struct Grid {
     Slot *blk64 = nullptr;          // [nslots64 + kRecPad]
     int32_t *blk64_off = nullptr;   // [M + 1] where each cell's FP64 block starts
     int64_t nslots64 = 0;
+    int64_t nslots = 0;             // slots of blk before the padding
     double build_ms = 0;
     int64_t device_bytes = 0;
     int device = 0;
