@@ -60,7 +60,8 @@ struct __attribute__((packed, aligned(8))) Rec24 {
 
 // Loads the block at offset b: its header, and this lane's first records
 // (record lane + W * r in round r). They are asked for before the row's
-// length is known; what lies past the end of the blocks is not read.
+// length is known; where that would be past the end of the blocks, the first
+// one instead (kRecPad slots of padding: it can always be read).
 template <int MODE, int W>
 __device__ __forceinline__ void load_cell(const GridRef &G, int32_t b, GroupCell<MODE> &C)
 {
@@ -73,21 +74,18 @@ __device__ __forceinline__ void load_cell(const GridRef &G, int32_t b, GroupCell
     const int4 s2 = *reinterpret_cast<const int4 *>(B + 2);
 #pragma unroll
     for (int r = 0; r < kGroupRounds; ++r) {
-        const int i = li + W * r;
         constexpr int bytes = record_bytes<MODE>();
-        const bool in = kHdrSlots + (bytes * (i + 1) + 15) / 16 <= slots;
+        int i = li + W * r;
+        i = kHdrSlots + (bytes * (i + 1) + 15) / 16 <= slots ? i : 0;
         if (MODE == VOR_MODE_FP64) {
-            Rec24 x = {0.0, 0.0, 0.0};
-            if (in) x = *reinterpret_cast<const Rec24 *>(rec + bytes * i);
+            const Rec24 x = *reinterpret_cast<const Rec24 *>(rec + bytes * i);
             C.d[r][0] = x.x;
             C.d[r][1] = x.y;
             C.d[r][2] = x.z;
         } else if (MODE == kModeCompact) {
-            C.q[r] = make_uint2(0u, 0u);
-            if (in) C.q[r] = *reinterpret_cast<const uint2 *>(rec + bytes * i);
+            C.q[r] = *reinterpret_cast<const uint2 *>(rec + bytes * i);
         } else {
-            Rec12 x = {0.0f, 0.0f, 0.0f};
-            if (in) x = *reinterpret_cast<const Rec12 *>(rec + bytes * i);
+            const Rec12 x = *reinterpret_cast<const Rec12 *>(rec + bytes * i);
             C.f[r][0] = x.x;
             C.f[r][1] = x.y;
             C.f[r][2] = x.z;
@@ -123,31 +121,41 @@ __device__ __forceinline__ int group_exit_fp64(F &&site, int n, const double pm[
                                                const double k[3], double L, double &best)
 {
     const int li = threadIdx.x & (W - 1);
+    constexpr int32_t kNone = 0x7fffffff;
     double bs = __builtin_huge_val(), bden = 0.0;
-    int32_t bi = 0x7fffffff;
+    int32_t bi = kNone;
+    // (& and | throughout: short-circuits would become branches)
     auto take = [&](int i, const Rec24 &q) {
         double den;
         const double s = cross_fp64(q.x, q.y, q.z, pm, r0, k, den);
-        if (i < n && den > 0.0 && s < L && (bi == 0x7fffffff || s < bs || (s == bs && den > bden))) {
-            bs = s;
-            bden = den;
-            bi = i;
-        }
+        const bool t = (i < n) & (den > 0.0) & (s < L) & ((bi == kNone) | (s < bs) | ((s == bs) & (den > bden)));
+        bs = t ? s : bs;
+        bden = t ? den : bden;
+        bi = t ? i : bi;
     };
 #pragma unroll
     for (int r = 0; r < kGroupRounds; ++r) take(li + W * r, site(r, li + W * r));
     for (int i = li + W * kGroupRounds; i < n; i += W) take(i, site(kGroupRounds, i));
-    group_exchange<W>([&](auto x) {
-        const double os = x.f64(bs), oden = x.f64(bden);
-        const int32_t oi = x.i32(bi);
-        const bool t = oi != 0x7fffffff &&
-                       (bi == 0x7fffffff || os < bs || (os == bs && (oden > bden || (oden == bden && oi < bi))));
-        bs = t ? os : bs;
-        bden = t ? oden : bden;
-        bi = t ? oi : bi;
-    });
-    best = bi == 0x7fffffff ? L : bs;
-    return bi == 0x7fffffff ? -1 : bi;
+    double least = bs;   // a lane without a candidate has +inf, which no crossing below L equals
+    group_exchange<W>([&](auto x) { least = fmin(least, x.f64(least)); });
+    const bool own = (bi != kNone) & (bs == least);
+    const uint32_t owners = group_bits<W>(__ballot(own));
+    if (__ballot((owners & (owners - 1u)) != 0u)) {   // some group has equal crossings
+        bden = own ? bden : -1.0;
+        bi = own ? bi : kNone;
+        group_exchange<W>([&](auto x) {
+            const double od = x.f64(bden);
+            const int32_t oi = x.i32(bi);
+            const bool t = (od > bden) | ((od == bden) & (oi < bi));
+            bden = t ? od : bden;
+            bi = t ? oi : bi;
+        });
+    } else {
+        bi = own ? bi : 0;
+        group_exchange<W>([&](auto x) { bi |= x.i32(bi); });
+    }
+    best = owners ? least : L;
+    return owners ? bi : -1;
 }
 
 // Mixed-precision exit search (exit_mixed and exit_mixed_compact): the
@@ -176,17 +184,17 @@ __device__ __forceinline__ int group_exit_mixed(const GridRef &G, const GroupCel
     float t1 = li == 0 ? tw : inf, err1 = li == 0 ? ew : 0.0f;
     int32_t w1 = li == 0 ? -1 : 0x7fffffff;
     float lo_a = li == 0 ? tw - ew : inf, lo_b = inf;
-    int32_t graze = 0;
+    bool graze = false;
     auto rank = [&](int i, float nx, float ny, float nz) {
         float t, err;
         bool pos, maybe;
         if (MODE == kModeCompact) plane_bound32q(nx, ny, nz, Qq, t, err, pos, maybe);
         else plane_bound32(nx, ny, nz, Q, t, err, pos, maybe);
         const bool in = i < C.n;
-        pos = pos && in;
-        graze |= (maybe && in && !pos) ? 1 : 0;
+        pos = pos & in;
+        graze |= maybe & in & !pos;
         const float lo = pos ? t - err : inf;
-        const bool w = pos && t < t1;
+        const bool w = pos & (t < t1);
         t1 = w ? t : t1;
         err1 = w ? err : err1;
         w1 = w ? i : w1;
@@ -213,28 +221,33 @@ __device__ __forceinline__ int group_exit_mixed(const GridRef &G, const GroupCel
             rank(i, x.x, x.y, x.z);
         }
     }
+    float least = t1;
     group_exchange<W>([&](auto x) {
-        const float ot = x.f32(t1), oe = x.f32(err1), oa = x.f32(lo_a), ob = x.f32(lo_b);
-        const int32_t ow = x.i32(w1);
-        graze |= x.i32(graze);
-        const bool t = ot < t1 || (ot == t1 && ow < w1);
-        t1 = t ? ot : t1;
-        err1 = t ? oe : err1;
-        w1 = t ? ow : w1;
-        lo_b = fminf(fmaxf(lo_a, oa), fminf(lo_b, ob));   // the two smallest of both halves
-        lo_a = fminf(lo_a, oa);
+        least = fminf(least, x.f32(least));
+        lo_b = fminf(fmaxf(lo_a, x.f32(lo_a)), fminf(lo_b, x.f32(lo_b)));   // the two smallest of both halves
+        lo_a = fminf(lo_a, x.f32(lo_a));
     });
-    const float lo1 = t1 - err1;
+    // The winner's bound and place, from the lane that has it. Two lanes with
+    // the same estimate mix theirs, to a bound no smaller than either (bits
+    // of positive floats): their intervals meet, so the step is redone.
+    const bool own = t1 == least;
+    uint32_t eb = own ? __float_as_uint(err1) : 0u, wb = own ? (uint32_t)(w1 + 1) : 0u;
+    group_exchange<W>([&](auto x) {
+        eb |= x.u32(eb);
+        wb |= x.u32(wb);
+    });
+    err1 = __uint_as_float(eb);
+    const float lo1 = least - err1;
     const float lo_other = (lo1 == lo_a) ? lo_b : lo_a;
-    redo = graze || !(t1 + err1 < lo_other);
-    return w1;
+    redo = (group_bits<W>(__ballot(graze)) != 0u) | !(least + err1 < lo_other);
+    return (int)wb - 1;
 }
 
 // Segments a group holds back: lane i has the i-th since the last write.
 struct GroupHeld {
     int32_t cell;
     double len;
-    int32_t n;            // how many
+    int32_t n, room;      // how many, and how many the run they are written in can take
     int64_t slot;         // where the first goes, -1 nowhere
     bool spill;
 };
@@ -275,18 +288,16 @@ template <int W, bool LP>
 __device__ __forceinline__ void group_segment(const SegOut &O, RayState &R, GroupHeld &H, int li, int64_t idx,
                                               int32_t cell, double len)
 {
-    if (H.n == 0) {
-        if (idx >= R.cap && (LP || O.spill_cell) && (idx - R.cap) % kSpillChunk == 0 && R.chunk != -2)
-            group_chunk<LP>(O, R, li, W);
+    if (H.n == 0) {   // a new run: to the end of the window or spill chunk, W at most
+        const int64_t past = idx - R.cap;
+        if (past >= 0 && (LP || O.spill_cell) && past % kSpillChunk == 0 && R.chunk != -2) group_chunk<LP>(O, R, li, W);
         H.slot = segment_slot<LP>(O, R, idx, H.spill);
+        const int64_t left = past < 0 ? -past : kSpillChunk - past % kSpillChunk;
+        H.room = left < W ? (int32_t)left : W;
     }
-    if (li == H.n) {
-        H.cell = cell;
-        H.len = len;
-    }
-    ++H.n;
-    const int64_t end = idx + 1 - R.cap;   // the window and every chunk start a new run
-    if (H.n == W || end == 0 || (end > 0 && end % kSpillChunk == 0)) group_write<LP>(O, H, li);
+    H.cell = li == H.n ? cell : H.cell;
+    H.len = li == H.n ? len : H.len;
+    if (++H.n == H.room) group_write<LP>(O, H, li);
 }
 
 // Walks the ray whose set-up R holds (r0, k, L, s_c, window, status) from
@@ -317,7 +328,7 @@ __device__ __forceinline__ void group_walk(const GridRef &G, const RayIn &I, con
             reinterpret_cast<const char *>(group_blocks<MODE>(G) + C.b + kHdrSlots) + record_bytes<MODE>() * C.n);
         int32_t nb[kGroupRounds];
 #pragma unroll
-        for (int r = 0; r < kGroupRounds; ++r) nb[r] = li + W * r < C.n ? off[li + W * r] : 0;
+        for (int r = 0; r < kGroupRounds; ++r) nb[r] = off[li + W * r < C.n ? li + W * r : 0];   // (past the row: not used)
         double rho = 0.0;
         if (I.grid_rho) rho = C.rho;
         else if (I.density) rho = I.density[C.uid];

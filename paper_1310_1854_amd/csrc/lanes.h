@@ -29,12 +29,6 @@ __device__ __forceinline__ uint32_t dpp_u32(uint32_t v)
 }
 
 template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v)
-{
-    return __uint_as_float(dpp_u32<CTRL>(__float_as_uint(v)));
-}
-
-template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v)
 {
     const uint64_t u = (uint64_t)__double_as_longlong(v);
@@ -72,25 +66,40 @@ __device__ __forceinline__ double wave_max_f64(double v)
     return lane_f64(v, 63);
 }
 
-// Exchanges between the halves of a group of 2, 4, 8 and 16 lanes whose
-// halves already agree: quad permutes, then the mirrors of 8 and 16 lanes.
-// F gets the DPP control as a type and combines the lane's values with the
-// other half's.
+// Exchanges between the halves of a group of 8 or 16 lanes whose halves
+// already agree: quad permutes, then the mirrors of 8 and 16 lanes. F gets
+// the move as an object and combines the lane's values with the other
+// half's. Every lane of these moves has a source, so they may be folded into
+// the instruction that uses them.
 template <int CTRL>
-struct Dpp {
-    static __device__ __forceinline__ uint32_t u32(uint32_t v) { return dpp_u32<CTRL>(v); }
-    static __device__ __forceinline__ int32_t i32(int32_t v) { return (int32_t)dpp_u32<CTRL>((uint32_t)v); }
-    static __device__ __forceinline__ float f32(float v) { return dpp_f32<CTRL>(v); }
-    static __device__ __forceinline__ double f64(double v) { return dpp_f64<CTRL>(v); }
+struct Swap {
+    static __device__ __forceinline__ uint32_t u32(uint32_t v)
+    {
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+    }
+    static __device__ __forceinline__ int32_t i32(int32_t v) { return (int32_t)u32((uint32_t)v); }
+    static __device__ __forceinline__ float f32(float v) { return __uint_as_float(u32(__float_as_uint(v))); }
+    static __device__ __forceinline__ double f64(double v)
+    {
+        const uint64_t u = (uint64_t)__double_as_longlong(v);
+        return __longlong_as_double((long long)((uint64_t)u32((uint32_t)u) | ((uint64_t)u32((uint32_t)(u >> 32)) << 32)));
+    }
 };
 template <int W, class F>
 __device__ __forceinline__ void group_exchange(F &&f)
 {
     static_assert(W == 8 || W == 16, "groups of half a row or a row");
-    f(Dpp<0xB1>());    // quad_perm 1 0 3 2
-    f(Dpp<0x4E>());    // quad_perm 2 3 0 1
-    f(Dpp<0x141>());   // row_half_mirror
-    if (W == 16) f(Dpp<0x140>());   // row_mirror
+    f(Swap<0xB1>());    // quad_perm 1 0 3 2
+    f(Swap<0x4E>());    // quad_perm 2 3 0 1
+    f(Swap<0x141>());   // row_half_mirror
+    if (W == 16) f(Swap<0x140>());   // row_mirror
+}
+
+// The bits of a ballot that belong to this lane's group.
+template <int W>
+__device__ __forceinline__ uint32_t group_bits(uint64_t ballot)
+{
+    return (uint32_t)(ballot >> (threadIdx.x & 63 & ~(W - 1))) & ((1u << W) - 1u);
 }
 
 }  // namespace vrt

@@ -576,19 +576,27 @@ int resident_blocks_per_cu(K kernel)
     return n;
 }
 
-// Up to how many rays a launch gives each ray a group of lanes. Kernel times
-// of one ray per lane / per group (us, whole paths into windows, mixed):
-//   rays                    61        1000       20000       40000       80000
-//   exp. disc, 10^5     478/187    956/321   1019/520   1045/861   1077/1438
-//   flared disc, 10^6  1109/369   1452/498   1812/881  2026/1356   1991/2077
-//   clumpy, 3x10^6     1418/448   1854/614  2124/1209  2052/2029   2309/3591
-// and without segments 2022/1491 and 2181/2562 on the last one at 40000 and
-// 80000; in FP64 2629/2005 and 3302/3512 (1437/827 and 1626/1385 on the
-// first), with transport outputs 2144/2786 and 2730/4913 (mixed).
+// Up to how many rays a launch gives each ray a group of lanes: about where
+// one ray per lane becomes the faster one on some grid. Kernel times of one
+// ray per lane / per group (us):
+//   rays                       61      1000     20000      40000      80000     160000
+//   mixed, windows
+//     exp. disc, 10^5     478/153   956/277  1019/452   1045/732  1077/1239  1146/1417
+//     flared disc, 10^6  1109/306  1452/417  1812/802  2026/1203  1991/1823  2296/2834
+//     clumpy, 3x10^6     1418/358  1854/518 2124/1161  2052/1928  2309/3354  2689/3691
+//   FP64, windows
+//     exp. disc           612/135  1322/248  1332/398   1437/660  1626/1095  1647/1271
+//     flared disc        1293/268  1998/366  2668/719  2803/1099  3183/1677  3634/2558
+//     clumpy             1816/310  2250/450  2676/933  2629/1586  3302/2826  4819/3220
+// FP64 without segments, at 260000 and 400000: 1874/1322 and 2309/1875 on the
+// exponential disc, 6399/3824 and 7521/5721 on the clumpy medium. With the
+// transport outputs the tally atomics cost the groups more (they deposit
+// one by one): clumpy, 40000 and 80000 rays in FP64 2932/2499 and 3916/4347.
 template <int MODE, bool SEGS, bool EXT>
 constexpr int64_t group_max_rays()
 {
-    return !EXT && (MODE == VOR_MODE_FP64 || !SEGS) ? 1 << 16 : 1 << 15;
+    if (MODE == VOR_MODE_FP64) return EXT ? 40960 : SEGS ? 98304 : 262144;
+    return EXT ? 32768 : SEGS ? 40960 : 65536;
 }
 
 // Launch of the trace kernel: one ray per group of lanes, or the start cells

@@ -9,8 +9,9 @@ from paper_1310_1854_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-N = 65_600          # past the largest launch with groups (65536)
-SLICES = [(0, 1), (1, 64), (64, 1000), (1000, 33_768), (33_768, N)]   # 1 to 32768 rays
+N = 262_200         # past the largest launch with groups (262144 rays: FP64 without segments)
+CUTS = [0, 1, 64, 1000] + list(range(32_768, N, 32_768)) + [N]       # slices of 1 to 32768 rays
+SLICES = list(zip(CUTS[:-1], CUTS[1:]))
 
 
 @pytest.fixture(scope="module")
@@ -66,7 +67,7 @@ def test_group_transport_agrees(vrt, case, mode):
     stop[10:20] = 0.0
     stop[20:30] = float("nan")
     wgt = 0.5 + torch.rand(N, dtype=torch.float64, device="cuda", generator=gen)
-    kw = dict(mode=mode, segments="stride", seg_stride=24, spill_chunks=N, kappa=3.0, tallies=True, persistent=True,
+    kw = dict(mode=mode, segments="stride", seg_stride=24, spill_chunks=4 * N, kappa=3.0, tallies=True, persistent=True,
               enter=True)
     big = vrt.trace(g, o, d, rho, tau_stop=stop, weight=wgt, **kw)
     tl, ta = torch.zeros_like(rho), torch.zeros_like(rho)
