@@ -32,8 +32,7 @@
 #include <thread>
 #include <vector>
 
-#include "locate_core.h"
-#include "trace_core.h"
+#include "group_core.h"
 
 using namespace vrt;
 
@@ -317,6 +316,86 @@ __global__ void __launch_bounds__(256) k_serve(const GridRef *__restrict__ grids
     }
 }
 
+// The serving kernel of a class with too few rays in the launch to fill the
+// device: one ray per group of lanes (group_core.h), one block per chunk of
+// kGroupChunk rays. The block's last wave counts the chunk off its request.
+constexpr int kGroupLanes = 16;
+constexpr int kGroupChunk = 256 / kGroupLanes;
+template <int MODE>
+__global__ void __launch_bounds__(256) k_serve_group(const GridRef *__restrict__ grids,
+                                                     const LocView *__restrict__ locs,
+                                                     const ReqDev *__restrict__ reqs,
+                                                     const ChunkDev *__restrict__ chunks,
+                                                     unsigned long long *__restrict__ counters)
+{
+    constexpr int W = kGroupLanes;
+    __shared__ unsigned long long sum[3];
+    __shared__ int ended;
+    if (threadIdx.x < 3) sum[threadIdx.x] = 0;
+    if (threadIdx.x == 3) ended = 0;
+    __syncthreads();
+    const ChunkDev ch = chunks[blockIdx.x];
+    const ReqDev &rq = reqs[ch.req];
+    const int g = threadIdx.x / W, li = threadIdx.x & (W - 1);
+    if (g < ch.count) {
+        const int64_t ray = ch.first + g;
+        const GridRef &G = grids[ch.ctx >> 2];
+        const LocView &loc = locs[ch.ctx >> 2];
+        RayIn I = rq.in;
+        I.grid_rho = (ch.ctx >> 1) & 1;
+        SegOut O{};
+        O.cell = rq.seg_cell;
+        O.len = rq.seg_len;
+        O.pool = &rq.spill;
+        RayStats S;
+        RayState R;
+        double s0;
+        R.st = ray_setup<false>(G, I, ray, R.r0, R.k, R.L, s0);
+        R.tau = 0.0;
+        R.s_c = 0.0;
+        R.chunk = rq.seg_cell ? -1 : -2;   // tau only: no spill chunk is ever taken
+        R.ray = (int32_t)ray;
+        R.base = ray * rq.seg_stride;
+        R.cap = rq.seg_cell ? rq.seg_stride : 0;
+        if (rq.spill.first && li == 0) rq.spill.first[ray] = -1;   // no chunk yet (taking one overwrites it)
+        if (R.st == RAY_OK) {
+            double p[3];
+            start_point(R.r0, R.k, s0, p);
+            int32_t m = -1;
+            if (loc.start) m = nearest_in_blocks_wave<W>(loc, p);
+            if (m < 0) m = nearest_site_wave<W>(G.grid, p, nullptr);
+            R.s_c = s0;
+            group_walk<MODE, true, false, true, W>(G, I, O, Extras{}, R, S, m);
+        }
+        if (li == 0) {
+            if (R.cap > 0 && R.st == RAY_OK && S.cnt > R.cap && R.chunk == -2) {   // its spill chunks ran out
+                R.st = RAY_OVERFLOW;
+                atomicAdd(rq.overflow, 1);
+            }
+            rq.tau[ray] = R.tau;
+            rq.n_seg[ray] = S.cnt;
+            rq.status[ray] = R.st;
+            atomicAdd(&sum[0], (unsigned long long)S.cnt);
+            if (S.nfb) atomicAdd(&sum[1], (unsigned long long)S.nfb);
+            if (S.nredo) atomicAdd(&sum[2], (unsigned long long)S.nredo);
+        }
+    }
+    int at = 0;
+    if ((threadIdx.x & 63) == 0) at = __hip_atomic_fetch_add(&ended, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__shfl(at, 0, 64) == 3) {   // the block's last wave
+        chunk_complete(reqs, ch.req);
+        const int i = threadIdx.x & 63;
+        const unsigned long long v = i < 3 ? __hip_atomic_load(&sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0ull;
+        if (v) atomicAdd(&counters[i], v);
+    }
+}
+
+// Up to how many rays of a class (FP64, mixed, mixed over compact records) a
+// launch gives each ray a group of lanes. 12 requests of 256 to 65536 rays
+// over three grids, whole client loop: 6.23 ms with one ray per lane, 4.43 ms
+// with these; 12 of 64 to 1000 rays: 5.10 and 1.86 ms.
+constexpr int64_t kGroupServeRays[3] = {131072, 65536, 65536};
+
 __global__ void k_zero_launch(unsigned int *head, unsigned long long *counters, ReqCount *rc, int n_req)
 {
     if (threadIdx.x < 3) head[threadIdx.x] = 0;
@@ -516,6 +595,21 @@ struct vor_server {
         return r.mode == VOR_MODE_FP64 ? 0 : (grid_refs[r.grid].blk_off ? 2 : 1);
     }
 
+    // The chunks [first, first + n) of kernel class c.
+    template <int MODE>
+    void launch_class(Launch &L, int c, int first, int n, bool group, int resident)
+    {
+        if (n == 0) return;
+        if (group) {
+            hipLaunchKernelGGL(k_serve_group<MODE>, dim3(n), dim3(256), 0, L.stream, d_grids, d_locs, L.d_reqs,
+                               L.d_chunks + first, L.d_counters);
+        } else {
+            const int nb = std::max(1, std::min(resident, (n + 3) / 4));
+            hipLaunchKernelGGL(k_serve<MODE>, dim3(nb), dim3(256), 0, L.stream, d_grids, d_locs, L.d_reqs,
+                               L.d_chunks + first, n, L.d_head + c, L.d_counters);
+        }
+    }
+
     void launch_locked(Launch &L)
     {
         L.reqs.clear();
@@ -551,11 +645,20 @@ struct vor_server {
             const int ka = kernel_class(reqs[x]), kb = kernel_class(reqs[y]);
             return (ka != kb) ? ka < kb : reqs[x].grid < reqs[y].grid;
         });
+        int64_t cls_rays[3] = {0, 0, 0};
+        for (int64_t id : L.reqs) cls_rays[kernel_class(reqs[id])] += reqs[id].n;
+        bool group[3];   // classes with few rays in the launch: a group of lanes per ray, in small chunks
+        for (int c = 0; c < 3; ++c) {
+            group[c] = cls_rays[c] <= kGroupServeRays[c] &&
+                       nch_total + cls_rays[c] / kGroupChunk + (int64_t)L.reqs.size() <= kMaxLaunchChunks;
+            if (group[c]) nch_total += cls_rays[c] / kGroupChunk + (int64_t)L.reqs.size();   // chunks more, at most
+        }
         int nch = 0, ncls[3] = {0, 0, 0};   // chunks, and those of each kernel class
         for (size_t qi = 0; qi < L.reqs.size(); ++qi) {
             Request &r = reqs[L.reqs[qi]];
             const int q = (int)qi;
-            const int need = (int)((r.n + chunk - 1) / chunk);
+            const int64_t per = group[kernel_class(r)] ? kGroupChunk : chunk;
+            const int need = (int)((r.n + per - 1) / per);
             ReqDev &d = L.h_reqs[q];
             d.in = r.in;
             d.tau = r.tau;
@@ -577,8 +680,8 @@ struct vor_server {
             for (int c = 0; c < need; ++c) {
                 ChunkDev &ch = L.h_chunks[nch++];
                 ch.req = q;
-                ch.first = (int32_t)(c * chunk);
-                ch.count = (int32_t)std::min<int64_t>(chunk, r.n - (int64_t)c * chunk);
+                ch.first = (int32_t)(c * per);
+                ch.count = (int32_t)std::min<int64_t>(per, r.n - (int64_t)c * per);
                 ch.ctx = ctx;
             }
             r.state = Q_RUNNING;
@@ -604,22 +707,9 @@ struct vor_server {
                   hipMemcpyAsync(L.d_remaining, L.h_remaining, sizeof(int32_t) * nreq, hipMemcpyHostToDevice,
                                  L.stream) == hipSuccess;
         hipLaunchKernelGGL(k_zero_launch, dim3(1), dim3(256), 0, L.stream, L.d_head, L.d_counters, L.d_count, nreq);
-        if (ncls[0] > 0) {
-            const int nb = std::max(1, std::min(blocks64, (ncls[0] + 3) / 4));
-            hipLaunchKernelGGL(k_serve<VOR_MODE_FP64>, dim3(nb), dim3(256), 0, L.stream, d_grids, d_locs, L.d_reqs,
-                               L.d_chunks,
-                               ncls[0], L.d_head, L.d_counters);
-        }
-        if (ncls[1] > 0) {
-            const int nb = std::max(1, std::min(blocks, (ncls[1] + 3) / 4));
-            hipLaunchKernelGGL(k_serve<VOR_MODE_MIXED>, dim3(nb), dim3(256), 0, L.stream, d_grids, d_locs, L.d_reqs,
-                               L.d_chunks + ncls[0], ncls[1], L.d_head + 1, L.d_counters);
-        }
-        if (ncls[2] > 0) {
-            const int nb = std::max(1, std::min(blocks_c, (ncls[2] + 3) / 4));
-            hipLaunchKernelGGL(k_serve<kModeCompact>, dim3(nb), dim3(256), 0, L.stream, d_grids, d_locs, L.d_reqs,
-                               L.d_chunks + ncls[0] + ncls[1], ncls[2], L.d_head + 2, L.d_counters);
-        }
+        launch_class<VOR_MODE_FP64>(L, 0, 0, ncls[0], group[0], blocks64);
+        launch_class<VOR_MODE_MIXED>(L, 1, ncls[0], ncls[1], group[1], blocks);
+        launch_class<kModeCompact>(L, 2, ncls[0] + ncls[1], ncls[2], group[2], blocks_c);
         ok = ok && hipGetLastError() == hipSuccess &&
              hipMemcpyAsync(L.h_counters, L.d_counters, 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost,
                             L.stream) == hipSuccess &&
