@@ -32,10 +32,7 @@ __global__ void k_validate_keys(const double *__restrict__ sites, int64_t M, Box
     for (int a = 0; a < 3; ++a) {
         double x = sites[3 * i + a];
         if (!(x >= box.lo[a] && x <= box.hi[a])) ok = false;   // also rejects NaN
-        double f = ok ? (x - box.lo[a]) * scale : 0.0;
-        int q = (int)f;
-        q = q < 0 ? 0 : (q > (1 << kHilbertBits) - 1 ? (1 << kHilbertBits) - 1 : q);
-        c[a] = (uint32_t)q;
+        c[a] = ok ? key_coord(x, box.lo[a], scale) : 0u;
     }
     if (!ok) atomicOr(err, ERR_OUTSIDE);
     keys[i] = hilbert_key(c[0], c[1], c[2]);
@@ -72,6 +69,20 @@ __global__ void __launch_bounds__(256) k_gather_sites(const double *__restrict__
             b.hi[a] = fmax(b.hi[a], __shfl_xor(b.hi[a], off, 64));
         }
     if (i < M && i % kLeaf == 0) leaf[i / kLeaf] = b;
+}
+
+// The seed table from the sorted Hilbert keys: the first site of every
+// octree cube that has one.
+__global__ void k_seeds(const uint32_t *__restrict__ keys, int64_t M, int levels, int32_t *__restrict__ seed)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= M) return;
+    const uint32_t key = keys[i], before = i > 0 ? keys[i - 1] : 0u;
+    for (int l = levels; l > 0; --l) {
+        const int sh = 30 - 3 * l;
+        if (i > 0 && key >> sh == before >> sh) break;   // not the first there, nor in the cubes around it
+        seed[seed_base(l) + (key >> sh)] = (int32_t)i;
+    }
 }
 
 // A level of the box tree: box k covers the 64 boxes [64 k, 64 k + 64) below
@@ -670,6 +681,10 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         tree.level[v] = boxes[v] = dalloc<Box6>(tree.n[v], rc, tmp, A);
     }
     int *hdr = nullptr;
+    g.seed_levels = seed_levels_of(M);
+    g.key_scale = hscale;
+    const int64_t n_seed = seed_base(g.seed_levels + 1);
+    g.seed = dalloc<int32_t>(n_seed, rc, keep, A);
 
     auto fail = [&](vor_status s) {
         (void)hipStreamSynchronize(st);
@@ -696,6 +711,9 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     for (int v = 1; v < 3; ++v)
         hipLaunchKernelGGL(k_box_level, dim3((unsigned)tree.n[v]), dim3(64), 0, st, boxes[v - 1], tree.n[v - 1],
                            boxes[v]);
+
+    if (hipMemsetAsync(g.seed, 0xff, sizeof(int32_t) * n_seed, st) != hipSuccess) return fail(VOR_EDEVICE);
+    hipLaunchKernelGGL(k_seeds, dim3(blocks_for(M, T)), dim3(T), 0, st, keys, M, g.seed_levels, g.seed);
 
     // bucket the Hilbert-ordered sites (stable: within a bucket, Hilbert order)
     GridArg ga;
@@ -896,7 +914,8 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     tmp.clear();
     g.device_bytes = (int64_t)M * (sizeof(Site) * 2 + 4 * 2 + 1 + sizeof(int2) + 2 * sizeof(double)) + (B + 1) * 4 +
                      (g.nnz + kRecPad) * (int64_t)sizeof(Rec64) + (nslots + kRecPad) * (int64_t)sizeof(Slot) +
-                     (g.blk_off ? (M + 1) * 4 : 0) + (g.nslots64 + kRecPad) * (int64_t)sizeof(Slot) + (M + 1) * 4;
+                     (g.blk_off ? (M + 1) * 4 : 0) + (g.nslots64 + kRecPad) * (int64_t)sizeof(Slot) + (M + 1) * 4 +
+                     n_seed * 4;
     if (want_loc)
         g.device_bytes += (int64_t)M * 6 * (int64_t)sizeof(double) +
                           ((int64_t)g.loc_dims[0] * g.loc_dims[1] * g.loc_dims[2] + 1 + g.loc_entries) * 4;
@@ -959,6 +978,7 @@ extern "C" vor_status vor_grid_truncate_row(vor_grid *G, int64_t site, int32_t k
         hipMemcpy(&rw, g.rows + i, sizeof(rw), hipMemcpyDeviceToHost) != hipSuccess)
         return VOR_EDEVICE;
     if (keep < rw.y) {
+        g.rows_cut = 1;   // no more walks along the table
         // the block offsets follow the records (12 or 8 bytes each): move the
         // first keep of them to their place after the first keep records
         int32_t bo = block_of(rw, i);

@@ -176,6 +176,100 @@ __device__ inline int32_t nearest_site_wave(const BucketGridView &g, const doubl
     return best_i;
 }
 
+// The nearest site by a walk along the neighbour table.
+struct WalkView {
+    const Slot *blk64;      // FP64 cell blocks
+    const int32_t *blk64_off;
+    const int32_t *seed;
+    int32_t levels;
+    double lo[3], hi[3], scale;
+    double sure;            // 2e-11 of the box diagonal
+};
+
+inline WalkView walk_view(const Grid &g)
+{
+    WalkView V;
+    V.blk64 = g.blk64;
+    V.blk64_off = g.blk64_off;
+    V.seed = g.seed;
+    V.levels = g.seed_levels;
+    double d2 = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        V.lo[a] = g.box[a];
+        V.hi[a] = g.box[a + 3];
+        d2 += (g.box[a + 3] - g.box[a]) * (g.box[a + 3] - g.box[a]);
+    }
+    V.scale = g.key_scale;
+    V.sure = 2e-11 * sqrt(d2);
+    return V;
+}
+
+// C(r) by a walk: from a site near q (the first one of the smallest occupied
+// octree cube around it) to whichever neighbour is nearest to q, until none
+// is nearer than the cell's own site. That site is the nearest of all when q
+// lies inside the cell by a margin that covers the rounding of the distances
+// and of the table: for every neighbour, d_j^2 - d_m^2 -- twice |n_j| times
+// the distance of q from the bisector -- exceeds |n_j| (2e-9 d_m + 2e-11 of
+// the box diagonal), and |n_j| exceeds 1e-5 d_m. (A ball around q of more
+// than the table's own tolerance then lies in the cell, so no other site's
+// bisector comes nearer, and none of them is so close to the cell's site
+// that the computed distances could not tell them apart: the neighbours'
+// bisectors leave a ball of 5e-6 d_m around it.) Returns -1 when the margin
+// is not there (on or next to a boundary, as lattice points are): the caller
+// then searches. The user index goes to *uid.
+__device__ __forceinline__ int32_t walk_to_site(const WalkView &V, const double q[3], int32_t *uid)
+{
+    const uint32_t key = hilbert_key(key_coord(q[0], V.lo[0], V.scale), key_coord(q[1], V.lo[1], V.scale),
+                                     key_coord(q[2], V.lo[2], V.scale));
+    int32_t m = -1;
+    for (int l = V.levels; m < 0 && l > 0; --l) m = V.seed[seed_base(l) + (key >> (30 - 3 * l))];
+    int32_t b = V.blk64_off[m < 0 ? 0 : m];
+    for (int step = 0; step < 128; ++step) {
+        const Slot *B = V.blk64 + b;
+        const double2 s0 = *reinterpret_cast<const double2 *>(B);
+        const double2 s1 = *reinterpret_cast<const double2 *>(B + 1);
+        const int4 s2 = *reinterpret_cast<const int4 *>(B + 2);
+        const int n = s2.z;
+        const double ex = q[0] - s0.x, ey = q[1] - s0.y, ez = q[2] - s1.x;
+        const double d2m = ex * ex + ey * ey + ez * ez;
+        const double c = 2e-9 * sqrt(d2m) + V.sure, c2 = c * c;
+        double best = d2m;
+        int w = -1;
+        bool sure = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) sure &= (q[a] - V.lo[a] > c) & (V.hi[a] - q[a] > c);
+        const double2 *rec = reinterpret_cast<const double2 *>(B + kHdrSlots);
+        for (int e0 = 0; e0 < n; e0 += 4) {   // 4 sites are 6 aligned 16-byte loads; past the row end masked
+            double p[12];
+#pragma unroll
+            for (int u = 0; u < 6; ++u) {
+                const double2 x = rec[3 * e0 / 2 + u];
+                p[2 * u] = x.x;
+                p[2 * u + 1] = x.y;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double dx = q[0] - p[3 * u], dy = q[1] - p[3 * u + 1], dz = q[2] - p[3 * u + 2];
+                const double d2 = dx * dx + dy * dy + dz * dz;
+                const double nx = p[3 * u] - s0.x, ny = p[3 * u + 1] - s0.y, nz = p[3 * u + 2] - s1.x;
+                const double n2 = nx * nx + ny * ny + nz * nz;
+                const bool in = e0 + u < n;
+                const double gap = d2 - d2m;
+                sure &= !in | ((gap > 0.0) & (gap * gap > n2 * c2) & (n2 > 1e-10 * d2m));
+                const bool t = in & (d2 < best);
+                best = t ? d2 : best;
+                w = t ? e0 + u : w;
+            }
+        }
+        if (w < 0) {
+            *uid = s2.x;
+            return sure ? s2.y : -1;
+        }
+        b = reinterpret_cast<const int32_t *>(reinterpret_cast<const double *>(rec) + 3 * n)[w];
+    }
+    return -1;
+}
+
 // The start cell of the ray on each lane, whose path starts at q (ok: the
 // ray has a path; else -1): through the block lists when the grid has them
 // (a point they cannot place falls back to the ring search), else the ring

@@ -113,6 +113,13 @@ struct Grid {
     int32_t *blk64_off = nullptr;   // [M + 1] where each cell's FP64 block starts
     int64_t nslots64 = 0;
     int64_t nslots = 0;             // slots of blk before the padding
+    // where a walk to the cell of a point starts: for each cube of an octree
+    // over the Hilbert order, levels 1 to seed_levels one after another, the
+    // first of its sites, or -1
+    int32_t *seed = nullptr;
+    int32_t seed_levels = 0;
+    double key_scale = 0;           // Hilbert-key units per unit length
+    int32_t rows_cut = 0;           // vor_grid_truncate_row has damaged the neighbour table
     double build_ms = 0;
     int64_t device_bytes = 0;
     int device = 0;
@@ -291,6 +298,25 @@ __device__ __forceinline__ uint32_t hilbert_key(uint32_t x, uint32_t y, uint32_t
     for (int b = kHilbertBits10 - 1; b >= 0; --b)
         key = (key << 3) | (((X[0] >> b) & 1u) << 2) | (((X[1] >> b) & 1u) << 1) | ((X[2] >> b) & 1u);
     return key;
+}
+
+
+// Entries of the seed table before level l (l >= 1): 8 + 8^2 + ... + 8^(l-1).
+VRT_HD inline int64_t seed_base(int l) { return (((int64_t)1 << (3 * l)) - 8) / 7; }
+
+// Levels of the seed table of M sites: about a cube per site at the last.
+inline int seed_levels_of(int64_t M)
+{
+    int l = 1;
+    while (l < 8 && ((int64_t)1 << (3 * l)) < M) ++l;
+    return l;
+}
+
+// A coordinate in Hilbert-key units.
+__device__ __forceinline__ uint32_t key_coord(double x, double lo, double scale)
+{
+    const int q = (int)((x - lo) * scale);
+    return (uint32_t)(q < 0 ? 0 : (q > (1 << kHilbertBits10) - 1 ? (1 << kHilbertBits10) - 1 : q));
 }
 
 
