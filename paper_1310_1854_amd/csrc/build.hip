@@ -245,113 +245,148 @@ __device__ __forceinline__ void loc_range(const LocArgs &A, int64_t i, int b0[3]
     }
 }
 
-__global__ void k_loc_count(LocArgs A, int32_t *__restrict__ cnt, unsigned long long *__restrict__ total)
+// One cell per 16 lanes, which share out the blocks of its box, z fastest
+// (one cell per lane leaves the wave waiting for its largest box: sparse cells
+// next to a dense disc have boxes of thousands of blocks).
+constexpr int kRowLanes = 16;
+template <class F>
+__device__ __forceinline__ int64_t loc_each(const LocArgs &A, int64_t i, F &&f)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= A.M) return;
     int b0[3], b1[3];
     loc_range(A, i, b0, b1);
-    for (int x = b0[0]; x <= b1[0]; ++x)
-        for (int y = b0[1]; y <= b1[1]; ++y)
-            for (int z = b0[2]; z <= b1[2]; ++z) atomicAdd(&cnt[((int64_t)x * A.dims[1] + y) * A.dims[2] + z], 1);
-    atomicAdd(total, (unsigned long long)(b1[0] - b0[0] + 1) * (b1[1] - b0[1] + 1) * (b1[2] - b0[2] + 1));
-}
-
-__global__ void k_loc_fill(LocArgs A, const int32_t *__restrict__ start, int32_t *__restrict__ cursor,
-                           int32_t *__restrict__ cells)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= A.M) return;
-    int b0[3], b1[3];
-    loc_range(A, i, b0, b1);
-    for (int x = b0[0]; x <= b1[0]; ++x)
-        for (int y = b0[1]; y <= b1[1]; ++y)
-            for (int z = b0[2]; z <= b1[2]; ++z) {
-                const int64_t k = ((int64_t)x * A.dims[1] + y) * A.dims[2] + z;
-                cells[start[k] + atomicAdd(&cursor[k], 1)] = (int32_t)i;
-            }
-}
-
-// Directed lists -> CSR (dir_start from a scan of cnt). slot[i] >= 0 marks a
-// site redone by the second pass; its list is in big_nbr at that slot.
-__global__ void k_gather_dir(const int32_t *__restrict__ nbr, const int32_t *__restrict__ cnt,
-                             const int32_t *__restrict__ dir_start, const int32_t *__restrict__ slot, int64_t M,
-                             const int32_t *__restrict__ big_nbr, int32_t *__restrict__ dir_col)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    int n = cnt[i];
-    int k = slot[i];
-    const int32_t *src = (k < 0) ? nbr + i * kMaxNbr : big_nbr + (int64_t)k * kMaxNbrBig;
-    int32_t *dst = dir_col + dir_start[i];
-    for (int e = 0; e < n; ++e) dst[e] = src[e];
-}
-
-__device__ __forceinline__ bool row_has(const int32_t *__restrict__ col, int s, int n, int32_t x)
-{
-    for (int e = 0; e < n; ++e)
-        if (col[s + e] == x) return true;
-    return false;
-}
-
-// For every directed entry i -> j whose reverse is missing, count an extra
-// entry for row j.
-__global__ void k_symm_count(const int32_t *__restrict__ dir_col, const int32_t *__restrict__ dir_start,
-                             const int32_t *__restrict__ cnt, int64_t M, int32_t *__restrict__ extra)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    int s = dir_start[i], n = cnt[i];
-    for (int e = 0; e < n; ++e) {
-        int32_t j = dir_col[s + e];
-        if (!row_has(dir_col, dir_start[j], cnt[j], (int32_t)i)) atomicAdd(&extra[j], 1);
+    const uint32_t nz = (uint32_t)(b1[2] - b0[2] + 1), ny = (uint32_t)(b1[1] - b0[1] + 1);
+    const int64_t n = (int64_t)(b1[0] - b0[0] + 1) * ny * nz;
+    for (int64_t q = threadIdx.x & (kRowLanes - 1); q < n; q += kRowLanes) {
+        const uint32_t u = (uint32_t)(q / nz), z = (uint32_t)(q - (int64_t)u * nz);
+        const uint32_t x = u / ny, y = u - x * ny;
+        f(((int64_t)(b0[0] + (int)x) * A.dims[1] + b0[1] + (int)y) * A.dims[2] + b0[2] + (int)z);
     }
+    return n;
 }
 
-__global__ void k_total_counts(const int32_t *__restrict__ cnt, const int32_t *__restrict__ extra, int64_t M,
-                               int32_t *__restrict__ total)
+__global__ void __launch_bounds__(256) k_loc_count(LocArgs A, int32_t *__restrict__ cnt,
+                                                   unsigned long long *__restrict__ total)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    total[i] = cnt[i] + extra[i];
+    __shared__ unsigned long long sum;
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
+    for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kRowLanes; i < A.M; i += (int64_t)gridDim.x * (256 / kRowLanes)) {
+        const int64_t n = loc_each(A, i, [&](int64_t k) { atomicAdd(&cnt[k], 1); });
+        if ((threadIdx.x & (kRowLanes - 1)) == 0) atomicAdd(&sum, (unsigned long long)n);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(total, sum);
 }
 
-// Copy each directed row to the front of its final row; cursor = its length.
-__global__ void k_copy_rows(const int32_t *__restrict__ dir_col, const int32_t *__restrict__ dir_start,
-                            const int32_t *__restrict__ cnt, const int32_t *__restrict__ start, int64_t M,
-                            int32_t *__restrict__ col, int32_t *__restrict__ cursor)
+__global__ void __launch_bounds__(256) k_loc_fill(LocArgs A, const int32_t *__restrict__ start,
+                                                  int32_t *__restrict__ cursor, int32_t *__restrict__ cells)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    int s = dir_start[i], n = cnt[i], o = start[i];
-    for (int e = 0; e < n; ++e) col[o + e] = dir_col[s + e];
-    cursor[i] = n;
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kRowLanes;
+    if (i < A.M) loc_each(A, i, [&](int64_t k) { cells[start[k] + atomicAdd(&cursor[k], 1)] = (int32_t)i; });
 }
 
-// Append the missing reverse entries (same test as k_symm_count).
-__global__ void k_symm_fill(const int32_t *__restrict__ dir_col, const int32_t *__restrict__ dir_start,
-                            const int32_t *__restrict__ cnt, const int32_t *__restrict__ start, int64_t M,
-                            int32_t *__restrict__ col, int32_t *__restrict__ cursor)
+// The rows as the clipping left them, each ascending: in the first pass's
+// table or, for sites redone with the large capacity (slot[i] >= 0), in
+// big_nbr at that slot; or, with col set, complete in CSR at offs[i].x.
+struct RowTable {
+    const int32_t *nbr;
+    const int32_t *cnt;
+    const int32_t *slot;
+    const int32_t *big_nbr;
+    const int32_t *col;
+    const int4 *offs;
+    __device__ const int32_t *row(int64_t i) const
+    {
+        if (col) return col + offs[i].x;
+        const int k = slot[i];
+        return k < 0 ? nbr + i * kMaxNbr : big_nbr + (int64_t)k * kMaxNbrBig;
+    }
+};
+
+__device__ __forceinline__ bool row_has(const int32_t *__restrict__ row, int n, int32_t x)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (row[mid] < x) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo < n && row[lo] == x;
+}
+
+// For every entry i -> j whose reverse is missing (hardly ever: a face at the
+// clipping's tolerance), count an extra entry for row j. kRowLanes lanes per
+// row.
+__global__ void __launch_bounds__(256) k_symm_count(RowTable T, int64_t M, int32_t *__restrict__ extra,
+                                                    int32_t *__restrict__ n_missing)
+{
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kRowLanes;
     if (i >= M) return;
-    int s = dir_start[i], n = cnt[i];
-    for (int e = 0; e < n; ++e) {
-        int32_t j = dir_col[s + e];
-        if (!row_has(dir_col, dir_start[j], cnt[j], (int32_t)i)) {
-            int pos = atomicAdd(&cursor[j], 1);
-            col[start[j] + pos] = (int32_t)i;
+    const int32_t *row = T.row(i);
+    const int n = T.cnt[i];
+    for (int e = threadIdx.x & (kRowLanes - 1); e < n; e += kRowLanes) {
+        const int32_t j = row[e];
+        if (!row_has(T.row(j), T.cnt[j], (int32_t)i)) {
+            atomicAdd(&extra[j], 1);
+            atomicAdd(n_missing, 1);
         }
     }
 }
 
-__global__ void k_row_sort(int32_t *__restrict__ col, const int32_t *__restrict__ start,
-                           const int32_t *__restrict__ total, int64_t M)
+__device__ __forceinline__ int wave_max_int(int v)
+{
+    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
+    return v;
+}
+
+// What each row takes: entries, slots of its FP64 block (the header, then 28
+// bytes per neighbour), slots of its compact block (12 bytes per neighbour;
+// blocks start on any slot: starting them on 64- or 128-byte lines was
+// measured slower), entries of the export (with walls); and the longest row.
+__global__ void __launch_bounds__(256) k_row_sizes(const int32_t *__restrict__ cnt, const int32_t *__restrict__ extra,
+                                                   const uint8_t *__restrict__ walls, int64_t M,
+                                                   int4 *__restrict__ sizes, int *__restrict__ max_row)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int n = 0;
+    if (i < M) {
+        n = cnt[i] + extra[i];
+        sizes[i] = make_int4(n, kHdrSlots + (7 * n + 3) / 4, kHdrSlots + (3 * n + 3) / 4, n + __popc((unsigned)walls[i]));
+    }
+    const int m = wave_max_int(n);
+    if ((threadIdx.x & 63) == 0 && m > __hip_atomic_load(max_row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(max_row, m);
+}
+
+// Rows with entries missing: each row to the front of its place in CSR
+// (cursor = its length), the missing reverses after it, then sorted.
+__global__ void k_copy_rows(RowTable T, int64_t M, int32_t *__restrict__ col, int32_t *__restrict__ cursor)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= M) return;
-    int32_t *row = col + start[i];
-    int n = total[i];
+    const int32_t *row = T.row(i);
+    const int n = T.cnt[i], o = T.offs[i].x;
+    for (int e = 0; e < n; ++e) col[o + e] = row[e];
+    cursor[i] = n;
+}
+
+__global__ void k_symm_fill(RowTable T, int64_t M, int32_t *__restrict__ col, int32_t *__restrict__ cursor)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= M) return;
+    const int32_t *row = T.row(i);
+    for (int e = 0; e < T.cnt[i]; ++e) {
+        const int32_t j = row[e];
+        if (!row_has(T.row(j), T.cnt[j], (int32_t)i)) col[T.offs[j].x + atomicAdd(&cursor[j], 1)] = (int32_t)i;
+    }
+}
+
+__global__ void k_row_sort(int32_t *__restrict__ col, const int4 *__restrict__ offs, int64_t M)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= M) return;
+    int32_t *row = col + offs[i].x;
+    const int n = offs[i + 1].x - offs[i].x;
     for (int a = 1; a < n; ++a) {
         int32_t x = row[a];
         int k = a - 1;
@@ -363,52 +398,56 @@ __global__ void k_row_sort(int32_t *__restrict__ col, const int32_t *__restrict_
     }
 }
 
-__device__ __forceinline__ int wave_max_int(int v)
+// The cell blocks, the FP64 records and the FP64 blocks, kRowLanes lanes per
+// row, so that a row's records leave as whole lines. Block i starts at
+// offs[i].z (compact) or block_of(row, i), its FP64 block at offs[i].y; each
+// header records the start of the cell's FP64 row. FP32 blocks hold the
+// offsets p_j - p_m rounded to FP32; compact blocks hold them as 21-bit
+// integers against the cell's scale 2^(E - 19), E the smallest exponent with
+// every offset component below 2^E (so |q| <= 2^19), but at least e_min, so
+// that the box in the cell's units stays far inside the FP32 range; rounding
+// to the nearest integer leaves each component within half a unit of the
+// scale. FP64 blocks hold the neighbour sites in the row's order (ascending
+// internal index). The neighbours' block offsets follow the records.
+struct FillArgs {
+    const Site *sites;
+    RowTable rows_in;
+    int64_t M;
+    int2 *rows;
+    Rec64 *r64;
+    Slot *blk, *blk64;
+    int32_t *blk_off, *blk64_off;   // blk_off null: FP32 blocks
+    int e_min;
+};
+__global__ void __launch_bounds__(256) k_fill_rows(FillArgs A)
 {
-    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
-// Slots of a compact cell block: the header, then 12 bytes per neighbour
-// (8-byte record + block offset), rounded up to whole slots. (Blocks start
-// on any slot: starting them on 64- or 128-byte lines was measured slower.)
-__global__ void k_compact_slots(const int32_t *__restrict__ total, int64_t M, int32_t *__restrict__ slots)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < M) slots[i] = kHdrSlots + (3 * total[i] + 3) / 4;
-}
-
-// The cell blocks and the FP64 records. Block i starts at blk_off[i]
-// (compact) or block_of(row, i); each header records the start of the
-// cell's FP64 row. FP32 blocks hold the offsets p_j - p_m rounded to FP32;
-// compact blocks hold them as 21-bit integers against the cell's scale
-// 2^(E - 19), E the smallest exponent with every offset component below
-// 2^E (so |q| <= 2^19), but at least e_min, so that the box in the cell's
-// units stays far inside the FP32 range; rounding to the nearest integer
-// leaves each component within half a unit of the scale.
-__global__ void k_fill_records(const Site *__restrict__ sites, const int32_t *__restrict__ col,
-                               const int32_t *__restrict__ total, const int32_t *__restrict__ start, int64_t M,
-                               int2 *__restrict__ rows, Rec64 *__restrict__ r64, Slot *__restrict__ blk,
-                               const int32_t *__restrict__ blk_off, int compact, int e_min,
-                               int *__restrict__ max_row)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int n = 0;
-    if (i < M) {
-        n = total[i];
-        int s0 = start[i];
-        rows[i] = make_int2(s0, n);
-        const Site si = sites[i];
-        const int32_t bo = blk_off ? blk_off[i] : block_of(make_int2(s0, n), (int32_t)i);
-        int E = 0;
-        if (compact) {
-            double mc = 0.0;
-            for (int e = 0; e < n; ++e) {
-                const Site sj = sites[col[s0 + e]];
-                mc = fmax(mc, fmax(fabs(sj.x - si.x), fmax(fabs(sj.y - si.y), fabs(sj.z - si.z))));
-            }
-            E = mc > 0.0 ? ilogb(mc) + 1 : e_min;
-            E = E < e_min ? e_min : (E > 127 ? 127 : E);
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kRowLanes;
+    const int li = threadIdx.x & (kRowLanes - 1);
+    if (i >= A.M) return;
+    const int4 o = A.rows_in.offs[i];
+    const int32_t *row = A.rows_in.row(i);
+    const int n = A.rows_in.offs[i + 1].x - o.x;
+    const Site si = A.sites[i];
+    const bool compact = A.blk_off != nullptr;
+    const int32_t bo = compact ? o.z : block_of(make_int2(o.x, n), (int32_t)i);
+    int E = 0;
+    if (compact) {
+        double mc = 0.0;
+        for (int e = li; e < n; e += kRowLanes) {
+            const Site sj = A.sites[row[e]];
+            mc = fmax(mc, fmax(fabs(sj.x - si.x), fmax(fabs(sj.y - si.y), fabs(sj.z - si.z))));
+        }
+        group_exchange<kRowLanes>([&](auto x) { mc = fmax(mc, x.f64(mc)); });
+        E = mc > 0.0 ? ilogb(mc) + 1 : A.e_min;
+        E = E < A.e_min ? A.e_min : (E > 127 ? 127 : E);
+    }
+    if (li == 0) {
+        A.rows[i] = make_int2(o.x, n);
+        A.blk64_off[i] = o.y;
+        if (compact) A.blk_off[i] = o.z;
+        if (i == A.M - 1) {   // the ends
+            A.blk64_off[A.M] = A.rows_in.offs[A.M].y;
+            if (compact) A.blk_off[A.M] = A.rows_in.offs[A.M].z;
         }
         BlockHdr h;
         h.x = si.x;
@@ -416,82 +455,48 @@ __global__ void k_fill_records(const Site *__restrict__ sites, const int32_t *__
         h.z = si.z;
         h.uid = (int32_t)si.uid;
         h.j = (int32_t)i;
-        h.len = n | (compact ? (E + kScaleBias) << 24 : 0);
-        h.row = s0;
+        h.row = o.x;
         h.rho = 0.0;
-        *reinterpret_cast<BlockHdr *>(blk + bo) = h;
-        float *rec = reinterpret_cast<float *>(blk + bo + kHdrSlots);           // FP32: n records of 3 floats
-        uint2 *crec = reinterpret_cast<uint2 *>(blk + bo + kHdrSlots);          // compact: n records of 8 bytes
-        int32_t *nb = compact ? reinterpret_cast<int32_t *>(crec + n) : reinterpret_cast<int32_t *>(rec + 3 * n);
-        const double sc = ldexp(1.0, kQShift - E);
-        for (int e = 0; e < n; ++e) {
-            int32_t j = col[s0 + e];
-            const Site sj = sites[j];
-            Rec64 a;
-            a.x = sj.x;
-            a.y = sj.y;
-            a.z = sj.z;
-            a.j = j;
-            a.uid = (int32_t)sj.uid;
-            r64[s0 + e] = a;
-            if (compact) {
-                const uint64_t m21 = (1ull << kQBits) - 1;
-                const uint64_t qx = (uint64_t)(int64_t)rint((sj.x - si.x) * sc) & m21;
-                const uint64_t qy = (uint64_t)(int64_t)rint((sj.y - si.y) * sc) & m21;
-                const uint64_t qz = (uint64_t)(int64_t)rint((sj.z - si.z) * sc) & m21;
-                const uint64_t v = qx | (qy << kQBits) | (qz << (2 * kQBits));
-                crec[e] = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
-            } else {
-                rec[3 * e] = (float)(sj.x - si.x);
-                rec[3 * e + 1] = (float)(sj.y - si.y);
-                rec[3 * e + 2] = (float)(sj.z - si.z);
-            }
-            nb[e] = blk_off ? blk_off[j] : block_of(make_int2(start[j], 0), j);
-        }
+        h.len = n;
+        *reinterpret_cast<BlockHdr *>(A.blk64 + o.y) = h;
+        h.len = n | (compact ? (E + kScaleBias) << 24 : 0);
+        *reinterpret_cast<BlockHdr *>(A.blk + bo) = h;
     }
-    int m = wave_max_int(n);
-    if ((threadIdx.x & 63) == 0) atomicMax(max_row, m);
-}
-
-// Slots of an FP64 cell block: the header, then 28 bytes per neighbour (its
-// FP64 site and block offset), rounded up to whole slots.
-__global__ void k_fp64_slots(const int2 *__restrict__ rows, int64_t M, int32_t *__restrict__ slots)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < M) slots[i] = kHdrSlots + (7 * rows[i].y + 3) / 4;
-}
-
-// FP64 cell blocks, what FP64-mode steps read: the header of the mixed-mode
-// blocks, then the cell's n neighbour sites in FP64 (24 bytes each, in the
-// row's order: ascending internal index), then the n neighbours' block
-// offsets. Block i starts at blk64_off[i].
-__global__ void k_fill_blk64(const Site *__restrict__ sites, const int2 *__restrict__ rows,
-                             const Rec64 *__restrict__ r64, const int32_t *__restrict__ blk64_off, int64_t M,
-                             Slot *__restrict__ blk64)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    const int2 rw = rows[i];
-    const int32_t bo = blk64_off[i];
-    const Site si = sites[i];
-    BlockHdr h;
-    h.x = si.x;
-    h.y = si.y;
-    h.z = si.z;
-    h.rho = 0.0;
-    h.uid = (int32_t)si.uid;
-    h.j = (int32_t)i;
-    h.len = rw.y;
-    h.row = rw.x;
-    *reinterpret_cast<BlockHdr *>(blk64 + bo) = h;
-    double *rec = reinterpret_cast<double *>(blk64 + bo + kHdrSlots);
-    int32_t *nb = reinterpret_cast<int32_t *>(rec + 3 * rw.y);
-    for (int e = 0; e < rw.y; ++e) {
-        const Rec64 a = r64[rw.x + e];
-        rec[3 * e] = a.x;
-        rec[3 * e + 1] = a.y;
-        rec[3 * e + 2] = a.z;
-        nb[e] = blk64_off[a.j];
+    float *rec = reinterpret_cast<float *>(A.blk + bo + kHdrSlots);    // FP32: n records of 3 floats
+    uint2 *crec = reinterpret_cast<uint2 *>(A.blk + bo + kHdrSlots);   // compact: n records of 8 bytes
+    int32_t *nb = compact ? reinterpret_cast<int32_t *>(crec + n) : reinterpret_cast<int32_t *>(rec + 3 * n);
+    double *rec64 = reinterpret_cast<double *>(A.blk64 + o.y + kHdrSlots);
+    int32_t *nb64 = reinterpret_cast<int32_t *>(rec64 + 3 * n);
+    const double sc = ldexp(1.0, kQShift - E);
+    for (int e = li; e < n; e += kRowLanes) {
+        const int32_t j = row[e];
+        const Site sj = A.sites[j];
+        const int4 oj = A.rows_in.offs[j];
+        Rec64 a;
+        a.x = sj.x;
+        a.y = sj.y;
+        a.z = sj.z;
+        a.j = j;
+        a.uid = (int32_t)sj.uid;
+        A.r64[o.x + e] = a;
+        rec64[3 * e] = sj.x;
+        rec64[3 * e + 1] = sj.y;
+        rec64[3 * e + 2] = sj.z;
+        nb64[e] = oj.y;
+        if (compact) {
+            const uint64_t m21 = (1ull << kQBits) - 1;
+            const uint64_t qx = (uint64_t)(int64_t)rint((sj.x - si.x) * sc) & m21;
+            const uint64_t qy = (uint64_t)(int64_t)rint((sj.y - si.y) * sc) & m21;
+            const uint64_t qz = (uint64_t)(int64_t)rint((sj.z - si.z) * sc) & m21;
+            const uint64_t v = qx | (qy << kQBits) | (qz << (2 * kQBits));
+            crec[e] = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+            nb[e] = oj.z;
+        } else {
+            rec[3 * e] = (float)(sj.x - si.x);
+            rec[3 * e + 1] = (float)(sj.y - si.y);
+            rec[3 * e + 2] = (float)(sj.z - si.z);
+            nb[e] = block_of(make_int2(oj.x, 0), j);
+        }
     }
 }
 
@@ -504,28 +509,53 @@ __global__ void k_export_counts(const int32_t *__restrict__ inv_perm, const int2
     cnt[u] = rows[i].y + __popc((unsigned)walls[i]);
 }
 
-__global__ void k_export_fill(const int32_t *__restrict__ inv_perm, const int32_t *__restrict__ perm,
-                              const int2 *__restrict__ rows, const Rec64 *__restrict__ r64,
-                              const uint8_t *__restrict__ walls, int64_t M, const int64_t *__restrict__ row_ptr,
-                              int32_t *__restrict__ col)
+// Rows of user indices, ascending, then walls: kRowLanes lanes per row, an
+// entry's place being the number of smaller ones in its row (rows too long
+// for their part of the LDS are sorted by their first lane).
+constexpr int kExportLds = 256;
+__global__ void __launch_bounds__(256) k_export_fill(const int32_t *__restrict__ inv_perm, const int2 *__restrict__ rows,
+                                                     const Rec64 *__restrict__ r64, const uint8_t *__restrict__ walls,
+                                                     int64_t M, const int64_t *__restrict__ row_ptr,
+                                                     int32_t *__restrict__ col)
 {
-    int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= M) return;
-    int32_t i = inv_perm[u];
-    int2 rw = rows[i];
-    int32_t *out = col + row_ptr[u];
-    for (int e = 0; e < rw.y; ++e) {
-        int32_t x = r64[rw.x + e].uid;
-        int k = e - 1;
-        while (k >= 0 && out[k] > x) {
-            out[k + 1] = out[k];
-            --k;
-        }
-        out[k + 1] = x;
+    __shared__ int32_t ids[256 / kRowLanes][kExportLds];
+    const int64_t u = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kRowLanes;
+    const int li = threadIdx.x & (kRowLanes - 1);
+    int32_t *id = ids[threadIdx.x / kRowLanes];
+    int2 rw = make_int2(0, 0);
+    int32_t i = 0;
+    if (u < M) {
+        i = inv_perm[u];
+        rw = rows[i];
+        if (rw.y <= kExportLds)
+            for (int e = li; e < rw.y; e += kRowLanes) id[e] = r64[rw.x + e].uid;
     }
-    int n = rw.y;
-    for (int w = 0; w < 6; ++w)
-        if ((walls[i] >> w) & 1) out[n++] = -(w + 1);
+    __syncthreads();
+    if (u >= M) return;
+    int32_t *out = col + row_ptr[u];
+    if (rw.y <= kExportLds) {
+        for (int e = li; e < rw.y; e += kRowLanes) {
+            const int32_t x = id[e];
+            int r = 0;
+            for (int k = 0; k < rw.y; ++k) r += id[k] < x ? 1 : 0;
+            out[r] = x;
+        }
+    } else if (li == 0) {
+        for (int e = 0; e < rw.y; ++e) {
+            const int32_t x = r64[rw.x + e].uid;
+            int k = e - 1;
+            while (k >= 0 && out[k] > x) {
+                out[k + 1] = out[k];
+                --k;
+            }
+            out[k + 1] = x;
+        }
+    }
+    if (li == 0) {
+        int n = rw.y;
+        for (int w = 0; w < 6; ++w)
+            if ((walls[i] >> w) & 1) out[n++] = -(w + 1);
+    }
 }
 
 // Device memory of a grid: from the caller's allocator when one is given
@@ -640,7 +670,7 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     uint32_t *keys2 = dalloc<uint32_t>(M, rc, tmp, A);
     int32_t *vals2 = dalloc<int32_t>(M, rc, tmp, A);
     int32_t *hist = dalloc<int32_t>(2 * hist_len + 1, rc, tmp, A);
-    int *err = dalloc<int>(4, rc, tmp, A);
+    int *err = dalloc<int>(8, rc, tmp, A);   // error flags, -, sites to retry, touched, longest row, missing entries
     g.sites = dalloc<Site>(M, rc, keep, A);
     g.perm = dalloc<int32_t>(M, rc, keep, A);
     g.inv_perm = dalloc<int32_t>(M, rc, keep, A);
@@ -669,10 +699,9 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     int32_t *cnt0 = dalloc<int32_t>(M, rc, tmp, A);
     int32_t *retry = dalloc<int32_t>(M, rc, tmp, A);
     int32_t *slot = dalloc<int32_t>(M, rc, tmp, A);
-    int32_t *dir_start = dalloc<int32_t>(M + 1, rc, tmp, A);
     int32_t *extra = dalloc<int32_t>(M, rc, tmp, A);
-    int32_t *total = dalloc<int32_t>(M, rc, tmp, A);
-    int32_t *start = dalloc<int32_t>(M + 1, rc, tmp, A);
+    int4 *sizes = dalloc<int4>(M, rc, tmp, A);
+    int4 *offs = dalloc<int4>(M + 1, rc, tmp, A);
     BoxTree tree;   // boxes over runs of kLeaf sites, then over 64 boxes each
     Box6 *boxes[3];
     for (int v = 0; v < 3; ++v) {
@@ -680,7 +709,6 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         tree.n[v] = (below + per - 1) / per;
         tree.level[v] = boxes[v] = dalloc<Box6>(tree.n[v], rc, tmp, A);
     }
-    int *hdr = nullptr;
     g.seed_levels = seed_levels_of(M);
     g.key_scale = hscale;
     const int64_t n_seed = seed_base(g.seed_levels + 1);
@@ -694,7 +722,7 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         return s;
     };
     if (rc != VOR_OK) return fail(rc);
-    if (hipMemsetAsync(err, 0, 4 * sizeof(int), st) != hipSuccess) return fail(VOR_EDEVICE);
+    if (hipMemsetAsync(err, 0, 8 * sizeof(int), st) != hipSuccess) return fail(VOR_EDEVICE);
 
     const int T = 256;
     hipLaunchKernelGGL(k_validate_keys, dim3(blocks_for(M, T)), dim3(T), 0, st, sites, M, ba, hscale, keys, vals, err);
@@ -779,95 +807,56 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     }
     g.n_big = n_retry;
 
-    // directed lists as CSR
-    rc = vrt_scan_i32_to_i32(cnt0, M, dir_start, st);
-    if (rc != VOR_OK) return fail(rc);
-    int32_t nnz_dir = 0;
-    if (hipMemcpyAsync(&nnz_dir, dir_start + M, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return fail(VOR_EDEVICE);
-    int32_t *dir_col = dalloc<int32_t>(std::max<int32_t>(nnz_dir, 1), rc, tmp, A);
-    if (rc != VOR_OK) return fail(rc);
-    hipLaunchKernelGGL(k_gather_dir, dim3(blocks_for(M, T)), dim3(T), 0, st, nbr0, cnt0, dir_start, slot, M, big_nbr,
-                       dir_col);
-
-    // symmetric lists: add the reverse of every one-sided entry, sort rows
+    // symmetric rows: which reverse entries are missing, what every row takes, where it goes
+    RowTable rt{nbr0, cnt0, slot, big_nbr, nullptr, offs};
     if (hipMemsetAsync(extra, 0, sizeof(int32_t) * M, st) != hipSuccess) return fail(VOR_EDEVICE);
-    hipLaunchKernelGGL(k_symm_count, dim3(blocks_for(M, T)), dim3(T), 0, st, dir_col, dir_start, cnt0, M, extra);
-    hipLaunchKernelGGL(k_total_counts, dim3(blocks_for(M, T)), dim3(T), 0, st, cnt0, extra, M, total);
-    rc = vrt_scan_i32_to_i32(total, M, start, st);
+    hipLaunchKernelGGL(k_symm_count, dim3(blocks_for(M * kRowLanes, T)), dim3(T), 0, st, rt, M, extra, err + 5);
+    hipLaunchKernelGGL(k_row_sizes, dim3(blocks_for(M, T)), dim3(T), 0, st, cnt0, extra, g.wall_mask, M, sizes, err + 4);
+    rc = vrt_scan_int4(sizes, M, offs, st);
     if (rc != VOR_OK) return fail(rc);
-    int32_t nnz32 = 0;
-    if (hipMemcpyAsync(&nnz32, start + M, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
+    int4 ends;
+    int rflags[2] = {0, 0};
+    if (hipMemcpyAsync(&ends, offs + M, sizeof(ends), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipMemcpyAsync(rflags, err + 4, sizeof(rflags), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess)
         return fail(VOR_EDEVICE);
-    g.nnz = nnz32;
-    int32_t *col = dalloc<int32_t>(std::max<int32_t>(nnz32, 1), rc, tmp, A);
-    if (rc != VOR_OK) return fail(rc);
-    hipLaunchKernelGGL(k_copy_rows, dim3(blocks_for(M, T)), dim3(T), 0, st, dir_col, dir_start, cnt0, start, M, col,
-                       extra);
-    hipLaunchKernelGGL(k_symm_fill, dim3(blocks_for(M, T)), dim3(T), 0, st, dir_col, dir_start, cnt0, start, M, col,
-                       extra);
-    hipLaunchKernelGGL(k_row_sort, dim3(blocks_for(M, T)), dim3(T), 0, st, col, start, total, M);
+    g.nnz = ends.x;
+    g.nnz_walls = ends.w;
+    g.max_row = rflags[0];
+    if (rflags[1] > 0) {   // complete and sort them in CSR
+        int32_t *col = dalloc<int32_t>(std::max<int32_t>(ends.x, 1), rc, tmp, A);
+        if (rc != VOR_OK) return fail(rc);
+        hipLaunchKernelGGL(k_copy_rows, dim3(blocks_for(M, T)), dim3(T), 0, st, rt, M, col, extra);
+        hipLaunchKernelGGL(k_symm_fill, dim3(blocks_for(M, T)), dim3(T), 0, st, rt, M, col, extra);
+        hipLaunchKernelGGL(k_row_sort, dim3(blocks_for(M, T)), dim3(T), 0, st, col, offs, M);
+        rt.col = col;
+    }
 
     // cell blocks are addressed by 32-bit slot offsets; FP32 blocks take
-    // kHdrSlots + n slots, compact ones kHdrSlots + ceil(3n / 4)
+    // kHdrSlots + n slots, compact ones kHdrSlots + ceil(3n / 4), FP64 ones at
+    // most 4 + 7n / 4
     int64_t nslots = g.nnz + (int64_t)kHdrSlots * M;
     if (nslots + kRecPad > 0x7fffffffLL) return fail(VOR_ECAPACITY);   // compact blocks take no more slots
+    if ((int64_t)4 * M + 2 * g.nnz + kRecPad > 0x7fffffffLL) return fail(VOR_ECAPACITY);
     g.compact = layout == VOR_RECORDS_COMPACT || (layout == VOR_RECORDS_AUTO && nslots * 16 > kCompactAutoBytes);
     if (g.compact) {   // blocks not at rows[j].x + 3j: their starts are kept
         g.blk_off = dalloc<int32_t>(M + 1, rc, keep, A);
-        if (rc != VOR_OK) return fail(rc);
-        hipLaunchKernelGGL(k_compact_slots, dim3(blocks_for(M, T)), dim3(T), 0, st, total, M, slot);
-        rc = vrt_scan_i32_to_i32(slot, M, g.blk_off, st);
-        if (rc != VOR_OK) return fail(rc);
-        int32_t ns = 0;
-        if (hipMemcpyAsync(&ns, g.blk_off + M, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess)
-            return fail(VOR_EDEVICE);
-        nslots = ns;
+        nslots = ends.z;
     }
-    if (nslots + kRecPad > 0x7fffffffLL) return fail(VOR_ECAPACITY);
     g.nslots = nslots;
+    g.nslots64 = ends.y;
     g.rows = dalloc<int2>(M, rc, keep, A);
     g.rec64 = dalloc<Rec64>(g.nnz + kRecPad, rc, keep, A);
     g.blk = dalloc<Slot>(nslots + kRecPad, rc, keep, A);
+    g.blk64_off = dalloc<int32_t>(M + 1, rc, keep, A);
+    g.blk64 = dalloc<Slot>(g.nslots64 + kRecPad, rc, keep, A);
     if (rc != VOR_OK) return fail(rc);
     if (hipMemsetAsync(g.rec64 + g.nnz, 0, sizeof(Rec64) * kRecPad, st) != hipSuccess ||
-        hipMemsetAsync(g.blk + nslots, 0, sizeof(Slot) * kRecPad, st) != hipSuccess)
+        hipMemsetAsync(g.blk + nslots, 0, sizeof(Slot) * kRecPad, st) != hipSuccess ||
+        hipMemsetAsync(g.blk64 + g.nslots64, 0, sizeof(Slot) * kRecPad, st) != hipSuccess)
         return fail(VOR_EDEVICE);
-    hdr = err + 1;   // longest row
-    hipLaunchKernelGGL(k_fill_records, dim3(blocks_for(M, T)), dim3(T), 0, st, g.sites, col, total, start, M, g.rows,
-                       g.rec64, g.blk, g.blk_off, (int)g.compact, compact_min_exp(g.box), hdr);
-    // the FP64 blocks: at most 4 + 7n/4 slots per cell
-    if ((int64_t)4 * M + 2 * g.nnz + kRecPad > 0x7fffffffLL) return fail(VOR_ECAPACITY);
-    g.blk64_off = dalloc<int32_t>(M + 1, rc, keep, A);
-    if (rc != VOR_OK) return fail(rc);
-    hipLaunchKernelGGL(k_fp64_slots, dim3(blocks_for(M, T)), dim3(T), 0, st, g.rows, M, slot);
-    rc = vrt_scan_i32_to_i32(slot, M, g.blk64_off, st);
-    if (rc != VOR_OK) return fail(rc);
-    int32_t ns64 = 0;
-    if (hipMemcpyAsync(&ns64, g.blk64_off + M, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return fail(VOR_EDEVICE);
-    g.nslots64 = ns64;
-    g.blk64 = dalloc<Slot>((int64_t)ns64 + kRecPad, rc, keep, A);
-    if (rc != VOR_OK) return fail(rc);
-    if (hipMemsetAsync(g.blk64 + ns64, 0, sizeof(Slot) * kRecPad, st) != hipSuccess) return fail(VOR_EDEVICE);
-    hipLaunchKernelGGL(k_fill_blk64, dim3(blocks_for(M, T)), dim3(T), 0, st, g.sites, g.rows, g.rec64, g.blk64_off, M,
-                       g.blk64);
-    // size of the export with walls
-    hipLaunchKernelGGL(k_export_counts, dim3(blocks_for(M, T)), dim3(T), 0, st, g.inv_perm, g.rows, g.wall_mask, M,
-                       total);
-    rc = vrt_scan_i32_to_i32(total, M, start, st);
-    if (rc != VOR_OK) return fail(rc);
-    int32_t nnzw = 0, mrow = 0;
-    if (hipMemcpyAsync(&nnzw, start + M, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipMemcpyAsync(&mrow, hdr, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess)
-        return fail(VOR_EDEVICE);
-    g.nnz_walls = nnzw;
-    g.max_row = mrow;
+    const FillArgs fa{g.sites, rt, M, g.rows, g.rec64, g.blk, g.blk64, g.blk_off, g.blk64_off, compact_min_exp(g.box)};
+    hipLaunchKernelGGL(k_fill_rows, dim3(blocks_for(M * kRowLanes, T)), dim3(T), 0, st, fa);
 
     if (want_loc) {
         // blocks: about M / locc of them, cube-like
@@ -893,7 +882,8 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         if (hipMemsetAsync(lcnt, 0, sizeof(int32_t) * K, st) != hipSuccess ||
             hipMemsetAsync(ltot, 0, sizeof(unsigned long long), st) != hipSuccess)
             return fail(VOR_EDEVICE);
-        hipLaunchKernelGGL(k_loc_count, dim3(blocks_for(M, T)), dim3(T), 0, st, la, lcnt, ltot);
+        // (few blocks: their atomics on the total take turns)
+        hipLaunchKernelGGL(k_loc_count, dim3(std::min(blocks_for(M * kRowLanes, T), 4096u)), dim3(T), 0, st, la, lcnt, ltot);
         unsigned long long entries = 0;
         if (hipMemcpyAsync(&entries, ltot, sizeof(entries), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess)
@@ -904,7 +894,7 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         g.loc_cells = dalloc<int32_t>(std::max<unsigned long long>(entries, 1), rc, keep, A);
         if (rc != VOR_OK) return fail(rc);
         if (hipMemsetAsync(lcnt, 0, sizeof(int32_t) * K, st) != hipSuccess) return fail(VOR_EDEVICE);
-        hipLaunchKernelGGL(k_loc_fill, dim3(blocks_for(M, T)), dim3(T), 0, st, la, g.loc_start, lcnt, g.loc_cells);
+        hipLaunchKernelGGL(k_loc_fill, dim3(blocks_for(M * kRowLanes, T)), dim3(T), 0, st, la, g.loc_start, lcnt, g.loc_cells);
         if (hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess) return fail(VOR_EDEVICE);
         g.loc_entries = (int64_t)entries;
     }
@@ -963,7 +953,7 @@ extern "C" vor_status vor_grid_neighbors(const vor_grid *G, int64_t *row_ptr, in
                        g.M, col);
     vor_status rc = vrt_scan_i32_to_i64(col, g.M, row_ptr, st);
     if (rc != VOR_OK) return rc;
-    hipLaunchKernelGGL(k_export_fill, dim3(blocks_for(g.M, T)), dim3(T), 0, st, g.inv_perm, g.perm, g.rows, g.rec64,
+    hipLaunchKernelGGL(k_export_fill, dim3(blocks_for(g.M * kRowLanes, T)), dim3(T), 0, st, g.inv_perm, g.rows, g.rec64,
                        g.wall_mask, g.M, row_ptr, col);
     return hipGetLastError() == hipSuccess ? VOR_OK : VOR_EDEVICE;
 }

@@ -327,6 +327,7 @@ inline bool cuda_ok(hipError_t e) { return e == hipSuccess; }
 // scan.hip
 vor_status vrt_scan_i32_to_i64(const int32_t *counts, int64_t N, int64_t *offsets, hipStream_t st);
 vor_status vrt_scan_i32_to_i32(const int32_t *counts, int64_t N, int32_t *offsets, hipStream_t st);
+vor_status vrt_scan_int4(const int4 *counts, int64_t N, int4 *offsets, hipStream_t st);   // each component
 // sort.hip: stable LSD radix sort of (key, value) pairs, 32-bit keys of `bits` significant bits
 vor_status vrt_radix_sort_pairs(uint32_t *keys, int32_t *vals, uint32_t *keys_tmp, int32_t *vals_tmp,
                                 int64_t n, int bits, int32_t *hist_scratch, int64_t hist_len, hipStream_t st);
