@@ -13,6 +13,7 @@
 //     records (FP64 sites and FP32 offsets per neighbour, CSR by cell).
 #include <chrono>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "../../include/voronoi_rt_diag.h"
@@ -583,19 +584,36 @@ struct DevAlloc {
     }
 };
 
-template <typename T>
-T *dalloc(size_t n, vor_status &st, std::vector<DevBlock> &track, const DevAlloc &A)
-{
-    if (st != VOR_OK) return nullptr;
-    const size_t bytes = n * sizeof(T) > 0 ? n * sizeof(T) : 1;
-    void *p = A.get(bytes);
-    if (!p) {
-        st = VOR_ENOMEM;
-        return nullptr;
+// Several arrays in one allocation, each on a 256-byte boundary: an
+// allocation and its release cost tens to hundreds of microseconds each, so
+// a build makes four or five of them instead of one per array.
+struct Batch {
+    struct Part {
+        void *p;   // the pointer to set
+        size_t off;
+    };
+    std::vector<Part> parts;
+    size_t bytes = 0;
+    template <typename T>
+    void add(T *&p, size_t n)
+    {
+        p = nullptr;
+        parts.push_back(Part{&p, bytes});
+        bytes += (n * sizeof(T) + 255) & ~(size_t)255;
     }
-    track.push_back(DevBlock{p, bytes});
-    return (T *)p;
-}
+    bool alloc(std::vector<DevBlock> &track, const DevAlloc &A)
+    {
+        if (bytes == 0) return true;
+        char *base = (char *)A.get(bytes);
+        if (!base) return false;
+        track.push_back(DevBlock{base, bytes});
+        for (const Part &q : parts) {
+            char *at = base + q.off;
+            std::memcpy(q.p, &at, sizeof(at));
+        }
+        return true;
+    }
+};
 
 unsigned blocks_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
@@ -664,22 +682,6 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     double ext = std::max(box[3] - box[0], std::max(box[4] - box[1], box[5] - box[2]));
     double hscale = (double)(1 << kHilbertBits) / ext;
 
-    int64_t hist_len = vrt_radix_hist_len(M);
-    uint32_t *keys = dalloc<uint32_t>(M, rc, tmp, A);
-    int32_t *vals = dalloc<int32_t>(M, rc, tmp, A);
-    uint32_t *keys2 = dalloc<uint32_t>(M, rc, tmp, A);
-    int32_t *vals2 = dalloc<int32_t>(M, rc, tmp, A);
-    int32_t *hist = dalloc<int32_t>(2 * hist_len + 1, rc, tmp, A);
-    int *err = dalloc<int>(8, rc, tmp, A);   // error flags, -, sites to retry, touched, longest row, missing entries
-    g.sites = dalloc<Site>(M, rc, keep, A);
-    g.perm = dalloc<int32_t>(M, rc, keep, A);
-    g.inv_perm = dalloc<int32_t>(M, rc, keep, A);
-    g.wall_mask = dalloc<uint8_t>(M, rc, keep, A);
-    g.volume = dalloc<double>(M, rc, keep, A);
-    g.rho_int = dalloc<double>(M, rc, keep, A);
-    g.bucket_sites = dalloc<Site>(M, rc, keep, A);
-    if (want_loc) g.bbox = dalloc<double>((size_t)M * 6, rc, keep, A);
-
     // bucket grid dimensions: about `occ` sites per bucket, cube-like buckets
     double vol = (box[3] - box[0]) * (box[4] - box[1]) * (box[5] - box[2]);
     double hb = std::cbrt(vol * occ / (double)M);
@@ -693,26 +695,75 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         g.inv_h[a] = n / e;
         B *= n;
     }
-    int32_t *bcount = dalloc<int32_t>(B, rc, tmp, A);
-    g.bucket_start = dalloc<int32_t>(B + 1, rc, keep, A);
-    int32_t *nbr0 = dalloc<int32_t>((size_t)M * kMaxNbr, rc, tmp, A);
-    int32_t *cnt0 = dalloc<int32_t>(M, rc, tmp, A);
-    int32_t *retry = dalloc<int32_t>(M, rc, tmp, A);
-    int32_t *slot = dalloc<int32_t>(M, rc, tmp, A);
-    int32_t *extra = dalloc<int32_t>(M, rc, tmp, A);
-    int4 *sizes = dalloc<int4>(M, rc, tmp, A);
-    int4 *offs = dalloc<int4>(M + 1, rc, tmp, A);
-    BoxTree tree;   // boxes over runs of kLeaf sites, then over 64 boxes each
-    Box6 *boxes[3];
-    for (int v = 0; v < 3; ++v) {
-        const int64_t per = v == 0 ? kLeaf : 64, below = v == 0 ? M : tree.n[v - 1];
-        tree.n[v] = (below + per - 1) / per;
-        tree.level[v] = boxes[v] = dalloc<Box6>(tree.n[v], rc, tmp, A);
+    // block-list dimensions: about M / locc blocks, cube-like
+    LocArgs la;
+    int64_t K = 1;
+    if (want_loc) {
+        const double hl = std::cbrt(vol * locc / (double)M);
+        for (int a = 0; a < 3; ++a) {
+            const double e = box[a + 3] - box[a];
+            const int n = std::max(1, std::min((int)std::ceil(e / hl), 1024));
+            g.loc_dims[a] = la.dims[a] = n;
+            g.loc_inv_h[a] = la.inv_h[a] = n / e;
+            la.lo[a] = box[a];
+            la.ext[a] = e;
+            K *= n;
+        }
+        if (K >= 0x7fffffffLL) {
+            delete G;
+            return VOR_ECAPACITY;
+        }
     }
+    const int64_t hist_len = vrt_radix_hist_len(M);
     g.seed_levels = seed_levels_of(M);
     g.key_scale = hscale;
     const int64_t n_seed = seed_base(g.seed_levels + 1);
-    g.seed = dalloc<int32_t>(n_seed, rc, keep, A);
+    Batch kept, temps;
+    kept.add(g.sites, M);
+    kept.add(g.perm, M);
+    kept.add(g.inv_perm, M);
+    kept.add(g.wall_mask, M);
+    kept.add(g.volume, M);
+    kept.add(g.rho_int, M);
+    kept.add(g.bucket_sites, M);
+    kept.add(g.bucket_start, B + 1);
+    kept.add(g.seed, n_seed);
+    kept.add(g.rows, M);
+    kept.add(g.blk64_off, M + 1);
+    if (want_loc) {
+        kept.add(g.bbox, (size_t)M * 6);
+        kept.add(g.loc_start, K + 1);
+    }
+    uint32_t *keys, *keys2;
+    int32_t *vals, *vals2, *hist, *bcount, *nbr0, *cnt0, *retry, *slot, *extra, *lcnt = nullptr;
+    int *err;   // error flags, -, sites to retry, touched, longest row, missing entries
+    int4 *sizes, *offs;
+    unsigned long long *ltot = nullptr;
+    BoxTree tree;   // boxes over runs of kLeaf sites, then over 64 boxes each
+    Box6 *boxes[3];
+    temps.add(keys, M);
+    temps.add(vals, M);
+    temps.add(keys2, M);
+    temps.add(vals2, M);
+    temps.add(hist, 2 * hist_len + 1);
+    temps.add(err, 8);
+    temps.add(bcount, B);
+    temps.add(nbr0, (size_t)M * kMaxNbr);
+    temps.add(cnt0, M);
+    temps.add(retry, M);
+    temps.add(slot, M);
+    temps.add(extra, M);
+    temps.add(sizes, M);
+    temps.add(offs, M + 1);
+    for (int v = 0; v < 3; ++v) {
+        const int64_t per = v == 0 ? kLeaf : 64, below = v == 0 ? M : tree.n[v - 1];
+        tree.n[v] = (below + per - 1) / per;
+        temps.add(boxes[v], tree.n[v]);
+    }
+    if (want_loc) {
+        temps.add(lcnt, K);
+        temps.add(ltot, 1);
+    }
 
     auto fail = [&](vor_status s) {
         (void)hipStreamSynchronize(st);
@@ -721,7 +772,8 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         delete G;
         return s;
     };
-    if (rc != VOR_OK) return fail(rc);
+    if (!kept.alloc(keep, A) || !temps.alloc(tmp, A)) return fail(VOR_ENOMEM);
+    for (int v = 0; v < 3; ++v) tree.level[v] = boxes[v];
     if (hipMemsetAsync(err, 0, 8 * sizeof(int), st) != hipSuccess) return fail(VOR_EDEVICE);
 
     const int T = 256;
@@ -796,8 +848,9 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     const int n_retry = hflags[2];
     int32_t *big_nbr = nullptr;
     if (n_retry > 0) {
-        big_nbr = dalloc<int32_t>((size_t)n_retry * kMaxNbrBig, rc, tmp, A);
-        if (rc != VOR_OK) return fail(rc);
+        Batch more;
+        more.add(big_nbr, (size_t)n_retry * kMaxNbrBig);
+        if (!more.alloc(tmp, A)) return fail(VOR_ENOMEM);
         hipLaunchKernelGGL(k_clip_big, dim3((unsigned)n_retry), dim3(64), 0, st, ca, big_nbr, slot);
         if (hipMemcpyAsync(hflags, err, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
@@ -824,8 +877,10 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     g.nnz_walls = ends.w;
     g.max_row = rflags[0];
     if (rflags[1] > 0) {   // complete and sort them in CSR
-        int32_t *col = dalloc<int32_t>(std::max<int32_t>(ends.x, 1), rc, tmp, A);
-        if (rc != VOR_OK) return fail(rc);
+        Batch more;
+        int32_t *col;
+        more.add(col, ends.x);
+        if (!more.alloc(tmp, A)) return fail(VOR_ENOMEM);
         hipLaunchKernelGGL(k_copy_rows, dim3(blocks_for(M, T)), dim3(T), 0, st, rt, M, col, extra);
         hipLaunchKernelGGL(k_symm_fill, dim3(blocks_for(M, T)), dim3(T), 0, st, rt, M, col, extra);
         hipLaunchKernelGGL(k_row_sort, dim3(blocks_for(M, T)), dim3(T), 0, st, col, offs, M);
@@ -839,18 +894,17 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     if (nslots + kRecPad > 0x7fffffffLL) return fail(VOR_ECAPACITY);   // compact blocks take no more slots
     if ((int64_t)4 * M + 2 * g.nnz + kRecPad > 0x7fffffffLL) return fail(VOR_ECAPACITY);
     g.compact = layout == VOR_RECORDS_COMPACT || (layout == VOR_RECORDS_AUTO && nslots * 16 > kCompactAutoBytes);
+    Batch records;
     if (g.compact) {   // blocks not at rows[j].x + 3j: their starts are kept
-        g.blk_off = dalloc<int32_t>(M + 1, rc, keep, A);
+        records.add(g.blk_off, M + 1);
         nslots = ends.z;
     }
     g.nslots = nslots;
     g.nslots64 = ends.y;
-    g.rows = dalloc<int2>(M, rc, keep, A);
-    g.rec64 = dalloc<Rec64>(g.nnz + kRecPad, rc, keep, A);
-    g.blk = dalloc<Slot>(nslots + kRecPad, rc, keep, A);
-    g.blk64_off = dalloc<int32_t>(M + 1, rc, keep, A);
-    g.blk64 = dalloc<Slot>(g.nslots64 + kRecPad, rc, keep, A);
-    if (rc != VOR_OK) return fail(rc);
+    records.add(g.rec64, g.nnz + kRecPad);
+    records.add(g.blk, nslots + kRecPad);
+    records.add(g.blk64, g.nslots64 + kRecPad);
+    if (!records.alloc(keep, A)) return fail(VOR_ENOMEM);
     if (hipMemsetAsync(g.rec64 + g.nnz, 0, sizeof(Rec64) * kRecPad, st) != hipSuccess ||
         hipMemsetAsync(g.blk + nslots, 0, sizeof(Slot) * kRecPad, st) != hipSuccess ||
         hipMemsetAsync(g.blk64 + g.nslots64, 0, sizeof(Slot) * kRecPad, st) != hipSuccess)
@@ -859,26 +913,8 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     hipLaunchKernelGGL(k_fill_rows, dim3(blocks_for(M * kRowLanes, T)), dim3(T), 0, st, fa);
 
     if (want_loc) {
-        // blocks: about M / locc of them, cube-like
-        LocArgs la;
         la.bbox = g.bbox;
         la.M = M;
-        const double hl = std::cbrt(vol * locc / (double)M);
-        int64_t K = 1;
-        for (int a = 0; a < 3; ++a) {
-            const double e = box[a + 3] - box[a];
-            const int n = std::max(1, std::min((int)std::ceil(e / hl), 1024));
-            g.loc_dims[a] = la.dims[a] = n;
-            g.loc_inv_h[a] = la.inv_h[a] = n / e;
-            la.lo[a] = box[a];
-            la.ext[a] = e;
-            K *= n;
-        }
-        if (K >= 0x7fffffffLL) return fail(VOR_ECAPACITY);
-        int32_t *lcnt = dalloc<int32_t>(K, rc, tmp, A);
-        unsigned long long *ltot = dalloc<unsigned long long>(1, rc, tmp, A);
-        g.loc_start = dalloc<int32_t>(K + 1, rc, keep, A);
-        if (rc != VOR_OK) return fail(rc);
         if (hipMemsetAsync(lcnt, 0, sizeof(int32_t) * K, st) != hipSuccess ||
             hipMemsetAsync(ltot, 0, sizeof(unsigned long long), st) != hipSuccess)
             return fail(VOR_EDEVICE);
@@ -891,8 +927,9 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         if (entries >= 0x7fffffffULL) return fail(VOR_ECAPACITY);
         rc = vrt_scan_i32_to_i32(lcnt, K, g.loc_start, st);
         if (rc != VOR_OK) return fail(rc);
-        g.loc_cells = dalloc<int32_t>(std::max<unsigned long long>(entries, 1), rc, keep, A);
-        if (rc != VOR_OK) return fail(rc);
+        Batch lists;
+        lists.add(g.loc_cells, std::max<unsigned long long>(entries, 1));
+        if (!lists.alloc(keep, A)) return fail(VOR_ENOMEM);
         if (hipMemsetAsync(lcnt, 0, sizeof(int32_t) * K, st) != hipSuccess) return fail(VOR_EDEVICE);
         hipLaunchKernelGGL(k_loc_fill, dim3(blocks_for(M * kRowLanes, T)), dim3(T), 0, st, la, g.loc_start, lcnt, g.loc_cells);
         if (hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess) return fail(VOR_EDEVICE);
