@@ -33,12 +33,14 @@
 // there. (Small cells only; a table for 255 planes would fill the LDS, so
 // large cells compare the removed vertices pairwise.)
 //
-// What bounds it: instruction issue, with 5 waves per SIMD to hide the LDS
-// round trips. About 22 cuts of some 220 instructions per cell are half of
-// it, the walk through the boxes a third. On a flared disc of 10^6 sites this
-// takes 20.5 ms for the small cells and 4 ms for the 213 large ones (the
-// latency of the largest, 99 faces); rings of a uniform bucket grid with the
-// cell in LDS, as before, took 137 and 38 ms.
+// What bounds it: instruction issue, with 4 to 5 waves per SIMD to hide the
+// LDS round trips. About 22 cuts of some 220 instructions per cell are more
+// than half of it, the walk through the boxes a quarter. On a flared disc of
+// 10^6 sites this takes 17 ms for the small cells and 3.4 ms for the 213
+// large ones (the latency of the largest, 99 faces); rings of a uniform
+// bucket grid with the cell in LDS, as before, took 137 and 38 ms. The tests
+// against every vertex read them in FP32 from LDS, four ahead; broadcast from
+// the lanes' FP64 registers they took 3.4 ms more.
 #pragma once
 
 #include "lanes.h"
@@ -85,6 +87,9 @@ struct WaveCell {
     uint32_t key[kWait + 64];                 // high words of their squared distances
     int32_t chunk[kTable ? 1 : 64];           // large cells: those taken together
     uint8_t twin[kTable ? P * P : 1];         // [a * P + b]: the vertex with the directed edge a -> b
+    float4 ball[K * 64];    // every vertex in FP32 and scaled, with the squared radius of its (widened) ball;
+                            // where there is none, a ball that meets nothing (0, 0, 0, -1)
+    float4 met[kTable ? 1 : 3 * K * 64];      // large cells: the balls that the boxes at each level meet
     uint32_t list[kTable ? 1 : K * 64];       // large cells: removed vertices; all vertices at the end
     double v[kTable ? 1 : 3 * K * 64];        // large cells: the vertices at the end
 };
@@ -104,6 +109,7 @@ struct LaneVerts {
     uint64_t valid[K];      // wave-uniform: lanes whose vertex q is one of the cell's
     double r2;              // wave-uniform: bound on the largest squared vertex distance (at most 2^-20 above it)
     double sr;              // its square root
+    double sc;              // wave-uniform: a power of two that scales the box to about 1, for FP32
     int np;                 // wave-uniform: plane slots in use
     bool touch;             // wave-uniform: a cut passed through a vertex, to within its tolerance
 };
@@ -185,6 +191,31 @@ __device__ __forceinline__ void own_edges(C &c, uint32_t t, int vert)
     }
 }
 
+// Vertex `vert` in FP32: see ball_meets and cuts_now.
+template <class C>
+__device__ __forceinline__ void set_ball(C &c, const LaneVerts<C::kPerLane> &R, int vert, double x, double y, double z)
+{
+    const float fx = (float)(x * R.sc), fy = (float)(y * R.sc), fz = (float)(z * R.sc);
+    c.ball[vert] = make_float4(fx, fy, fz, fmaf(fx, fx, fmaf(fy, fy, fz * fz)) * 1.00002f);
+}
+
+template <class C>
+__device__ __forceinline__ void no_ball(C &c, int vert)
+{
+    c.ball[vert] = make_float4(0.0f, 0.0f, 0.0f, -1.0f);
+}
+
+// One past the last vertex in use.
+template <int K>
+__device__ __forceinline__ int verts_end(const LaneVerts<K> &R)
+{
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < K; ++q)
+        if (R.valid[q]) n = q * 64 + 64 - __clzll((long long)R.valid[q]);
+    return n;
+}
+
 // The box as the initial cell (6 wall planes, 8 corner vertices).
 template <class C>
 __device__ __forceinline__ void wcell_init(C &c, LaneVerts<C::kPerLane> &R, const double p[3], const BoxArg &box)
@@ -209,8 +240,15 @@ __device__ __forceinline__ void wcell_init(C &c, LaneVerts<C::kPerLane> &R, cons
         R.x[q] = R.y[q] = R.z[q] = 0.0;
         R.tri[q] = 0;
         R.valid[q] = 0;
+        no_ball(c, q * 64 + l);
     }
     R.valid[0] = 0xff;
+    lds_order();
+    {
+        double ext = 0.0;
+        for (int a = 0; a < 3; ++a) ext = fmax(ext, box.hi[a] - box.lo[a]);
+        R.sc = ldexp(1.0, -min(max(ilogb(ext), -1000), 1000));
+    }
     if (l < 8) {
         const int sx = l & 1, sy = (l >> 1) & 1, sz = (l >> 2) & 1;
         const int X = sx, Y = 2 + sy, Z = 4 + sz;
@@ -220,6 +258,7 @@ __device__ __forceinline__ void wcell_init(C &c, LaneVerts<C::kPerLane> &R, cons
         R.y[0] = sy ? (box.hi[1] - p[1]) : -(p[1] - box.lo[1]);
         R.z[0] = sz ? (box.hi[2] - p[2]) : -(p[2] - box.lo[2]);
         own_edges(c, R.tri[0], l);
+        set_ball(c, R, l, R.x[0], R.y[0], R.z[0]);
     }
     R.np = 6;
     R.touch = false;
@@ -346,13 +385,19 @@ __device__ __forceinline__ int wcell_cut(C &c, LaneVerts<C::kPerLane> &R, double
             bad = bad || !wvertex(c.pl[a], c.pl[b], pn, R.x[q], R.y[q], R.z[q]);
             R.tri[q] = wpack3(a, b, Pn);
             own_edges(c, R.tri[q], q * 64 + l);
+            set_ball(c, R, q * 64 + l, R.x[q], R.y[q], R.z[q]);
+        } else if ((off[q] >> l) & 1ull) {
+            no_ball(c, q * 64 + l);
         }
         R.valid[q] = keep | __ballot(take);
         base += 64 - __popcll(keep);
         if (K > 1 && base >= nrim) {   // the slots above keep what they hold
 #pragma unroll
             for (int q2 = 0; q2 < K; ++q2)
-                if (q2 > q) R.valid[q2] &= ~off[q2];
+                if (q2 > q) {
+                    if ((off[q2] >> l) & 1ull) no_ball(c, q2 * 64 + l);
+                    R.valid[q2] &= ~off[q2];
+                }
             break;
         }
     }
@@ -363,28 +408,32 @@ __device__ __forceinline__ int wcell_cut(C &c, LaneVerts<C::kPerLane> &R, double
     return 1;
 }
 
-// Which of the 64 candidates (one per lane: offset n, d = |n|^2 / 2) cut the
-// cell as it stands: the largest n.v - d over the vertices is above zero
-// (the cut itself asks for more than a small tolerance).
-template <int K>
-__device__ __forceinline__ bool cuts_now(const LaneVerts<K> &R, double nx, double ny, double nz, double d)
+// Which of the 64 candidates (one per lane: offset n, d = |n|^2 / 2) may cut
+// the cell as it stands: whether the largest n.v over the vertices exceeds d.
+// In FP32, with more than its rounding in hand, so that none is passed over
+// which the cut itself would take; what falls out of its range passes.
+template <class C>
+__device__ __forceinline__ bool cuts_now(const C &c, const LaneVerts<C::kPerLane> &R, double nx, double ny, double nz,
+                                         double d)
 {
-    double m = -__builtin_huge_val();
-#pragma unroll
-    for (int q = 0; q < K; ++q)
-        for (uint64_t left = R.valid[q]; left; left &= left - 1) {
-            const int t = __ffsll((long long)left) - 1;
-            const double vx = lane_f64(R.x[q], t), vy = lane_f64(R.y[q], t), vz = lane_f64(R.z[q], t);
-            m = fmax(m, __builtin_fma(nx, vx, __builtin_fma(ny, vy, nz * vz)));
-        }
-    return m > d;
+    const float fx = (float)(nx * R.sc), fy = (float)(ny * R.sc), fz = (float)(nz * R.sc);
+    const float fd = (float)(d * R.sc * R.sc), fr = (float)(R.sr * R.sc);
+    const float thr = fd * 0.999999f - 1e-6f * (fabsf(fx) + fabsf(fy) + fabsf(fz)) * fr;
+    float m = -__builtin_huge_valf();
+    const int end = verts_end(R);
+#pragma unroll 4
+    for (int k = 0; k < end; ++k) {   // no vertex there: 0, which decides nothing (thr > 0, or all pass)
+        const float4 v = c.ball[k];
+        m = fmaxf(m, fmaf(fx, v.x, fmaf(fy, v.y, fz * v.z)));
+    }
+    return !(m < thr);
 }
 
 // Takes a batch of candidates, one per lane (site offset n, squared distance
 // d2, site j, act: there is one), nearest first. cull: test them all against
 // the cell beforehand; after a candidate that cut nothing the rest are
 // tested again. Returns 0 or an -ERR_* code.
-constexpr int kCullMin = 8;   // fewer candidates are as well cut by one by one
+constexpr int kCullMin = 6;   // fewer candidates are as well cut by one by one
 template <class C>
 __device__ __forceinline__ int wcell_take(C &c, LaneVerts<C::kPerLane> &R, double nx, double ny, double nz, double d2,
                                           int32_t j, bool act, bool cull)
@@ -395,7 +444,7 @@ __device__ __forceinline__ int wcell_take(C &c, LaneVerts<C::kPerLane> &R, doubl
         uint64_t am = __ballot(act);
         if (am == 0) return 0;
         if (cull && __popcll(am) >= kCullMin) {
-            const bool cuts = cuts_now(R, nx, ny, nz, 0.5 * d2);   // by every lane: it broadcasts the vertices
+            const bool cuts = cuts_now(c, R, nx, ny, nz, 0.5 * d2);
             act = act && cuts;
             am = __ballot(act);
             if (am == 0) return 0;
@@ -431,62 +480,68 @@ __device__ __forceinline__ double box_dist2(const Box6 &b, const double p[3])
 struct BoxF {
     float lx, ly, lz, hx, hy, hz;
 };
-__device__ __forceinline__ BoxF box_f32(const Box6 &b, const double p[3], double slack)
+__device__ __forceinline__ BoxF box_f32(const Box6 &b, const double p[3], double slack, double sc)
 {
-    auto lo = [&](int a) { const float f = (float)(b.lo[a] - p[a] - slack); return f - 2.4e-7f * fabsf(f); };
-    auto hi = [&](int a) { const float f = (float)(b.hi[a] - p[a] + slack); return f + 2.4e-7f * fabsf(f); };
+    auto lo = [&](int a) { const float f = (float)((b.lo[a] - p[a] - slack) * sc); return f - 2.4e-7f * fabsf(f); };
+    auto hi = [&](int a) { const float f = (float)((b.hi[a] - p[a] + slack) * sc); return f + 2.4e-7f * fabsf(f); };
     return BoxF{lo(0), lo(1), lo(2), hi(0), hi(1), hi(2)};
 }
-__device__ __forceinline__ bool ball_meets(const BoxF &b, float vx, float vy, float vz, float r2)
+__device__ __forceinline__ bool ball_meets(const BoxF &b, const float4 &v)
 {
-    const float ex = fmaxf(fmaxf(b.lx - vx, vx - b.hx), 0.0f);
-    const float ey = fmaxf(fmaxf(b.ly - vy, vy - b.hy), 0.0f);
-    const float ez = fmaxf(fmaxf(b.lz - vz, vz - b.hz), 0.0f);
-    return !(fmaf(ex, ex, fmaf(ey, ey, ez * ez)) > r2);
+    const float ex = fmaxf(fmaxf(b.lx - v.x, v.x - b.hx), 0.0f);
+    const float ey = fmaxf(fmaxf(b.ly - v.y, v.y - b.hy), 0.0f);
+    const float ez = fmaxf(fmaxf(b.lz - v.z, v.z - b.hz), 0.0f);
+    return !(fmaf(ex, ex, fmaf(ey, ey, ez * ez)) > v.w);
 }
 
-// The vertices in FP32 with the squared radii of their (widened) balls.
-template <int K>
-struct LaneBalls {
-    float x[K], y[K], z[K], r2[K];
-    __device__ __forceinline__ void set(const LaneVerts<K> &R)
-    {
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            x[q] = (float)R.x[q];
-            y[q] = (float)R.y[q];
-            z[q] = (float)R.z[q];
-            r2[q] = fmaf(x[q], x[q], fmaf(y[q], y[q], z[q] * z[q])) * 1.00002f;
-        }
-    }
-};
-
-// Sets of the cell's vertices: bit l of m[q] is vertex q * 64 + l.
-template <int K>
-struct VertSet {
-    uint64_t m[K];
-};
-
-// The vertices of `of` that a site in the box (wave-uniform) may cut off.
-template <int K>
-__device__ __forceinline__ VertSet<K> verts_met(const LaneBalls<K> &F, const VertSet<K> &of, const BoxF &b)
+// The cell's balls, one after another, at the first level of met (large cells).
+template <class C>
+__device__ __forceinline__ int list_balls(C &c, const LaneVerts<C::kPerLane> &R)
 {
-    VertSet<K> s;
+    int n = 0;
+    if constexpr (!C::kTable) {
+        lds_order();
 #pragma unroll
-    for (int q = 0; q < K; ++q) s.m[q] = __ballot(ball_meets(b, F.x[q], F.y[q], F.z[q], F.r2[q])) & of.m[q];
-    return s;
+        for (int q = 0; q < C::kPerLane; ++q) {
+            if ((R.valid[q] >> lane_id()) & 1ull)
+                c.met[n + __popcll(R.valid[q] & lanemask_lt())] = c.ball[q * 64 + lane_id()];
+            n += __popcll(R.valid[q]);
+        }
+        lds_order();
+    }
+    return n;
+}
+
+// Of the n balls listed for level `at` of met, those that a box
+// (wave-uniform) meets, listed for the next level. Returns their number.
+template <class C>
+__device__ __forceinline__ int balls_met(C &c, int at, int n, const BoxF &b)
+{
+    constexpr int kList = C::kPerLane * 64;
+    int m = 0;
+    lds_order();
+    for (int e = 0; e < n; e += 64) {
+        const int k = e + lane_id();
+        const float4 v = c.met[at * kList + (k < n ? k : 0)];
+        const bool in = k < n && ball_meets(b, v);
+        const uint64_t bal = __ballot(in);
+        if (in) c.met[(at + 1) * kList + m + __popcll(bal & lanemask_lt())] = v;
+        m += __popcll(bal);
+    }
+    lds_order();
+    return m;
 }
 
 // 64 boxes of a level, one per lane, and which of them hold candidates at a
 // squared distance in [from, to): within the sphere of twice the largest
-// vertex distance and, where many are, in the ball of one of the vertices of
-// `of` (large cells: those that the boxes above them meet).
-// Boxes in the sphere from which the ball test pays: 12 / 16-20 / 32 / never
-// measured 32.6 / 32.7 / 36.3 / 41.5 ms for the whole build of a 10^6-site
-// flared disc, 49.7 / 49.1 / 49.5 / 50.0 ms for a clumpy medium of 2x10^6.
-constexpr int kBallMin = 16;
-template <int K>
-__device__ __forceinline__ uint64_t boxes_hit(const LaneVerts<K> &R, const LaneBalls<K> &F, const VertSet<K> &of,
+// vertex distance and, where many are, in the ball of one of the vertices
+// (large cells: of the n listed for level `at`, which the boxes above meet).
+// Boxes in the sphere from which the ball test pays: 6 / 10 / 16 measured
+// 22.4 / 22.0 / 22.1 ms for the whole build of a 10^6-site flared disc (never:
+// a quarter more), 35.5 / 35.1 / 34.9 ms for a clumpy medium of 2x10^6.
+constexpr int kBallMin = 12;
+template <class C>
+__device__ __forceinline__ uint64_t boxes_hit(const C &c, const LaneVerts<C::kPerLane> &R, int at, int n_balls,
                                               const Box6 *boxes, int64_t n, int64_t first, const double p[3],
                                               double from, double to, double slack, Box6 &b)
 {
@@ -507,14 +562,16 @@ __device__ __forceinline__ uint64_t boxes_hit(const LaneVerts<K> &R, const LaneB
     }
     uint64_t hit = __ballot(in);
     if (__popcll(hit) >= kBallMin) {
-        const BoxF f = box_f32(b, p, slack);
+        const BoxF f = box_f32(b, p, slack, R.sc);
         bool may = false;
-#pragma unroll
-        for (int q = 0; q < K; ++q)
-            for (uint64_t left = of.m[q]; left; left &= left - 1) {   // by every lane: it broadcasts the vertices
-                const int t = __ffsll((long long)left) - 1;
-                may |= ball_meets(f, lane_f32(F.x[q], t), lane_f32(F.y[q], t), lane_f32(F.z[q], t), lane_f32(F.r2[q], t));
-            }
+        if constexpr (C::kTable) {
+            const int end = verts_end(R);
+#pragma unroll 4
+            for (int k = 0; k < end; ++k) may |= ball_meets(f, c.ball[k]);
+        } else {
+#pragma unroll 4
+            for (int k = 0; k < n_balls; ++k) may |= ball_meets(f, c.met[at * C::kPerLane * 64 + k]);
+        }
         hit &= __ballot(may);
     }
     return hit;
@@ -749,22 +806,15 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
     while (M > 64) {
         int nbuf = 0;
         bool crowded = false;   // the shell was cut back
-        bool stale = false;   // the cell was cut in this pass: sets of vertices taken before are void
-        VertSet<K> all;
-        LaneBalls<K> F;
-        F.set(R);
-#pragma unroll
-        for (int q = 0; q < K; ++q) all.m[q] = R.valid[q];
-        // The vertices a box's sites may cut, for the boxes below it (few of
-        // a large cell's; small cells spare the registers).
-        auto below = [&](const VertSet<K> &of, const Box6 &boxes, int at, VertSet<K> &met) {
-            met = all;
-            if (K == 1 || stale) return true;
-            met = verts_met(F, of, box_f32(lane_box(boxes, at), p, slack));
-            uint64_t any = 0;
-#pragma unroll
-            for (int q = 0; q < K; ++q) any |= met.m[q];
-            return any != 0;
+        const int n_all = list_balls(c, R);
+        // The balls a box's sites may lie in, for the boxes below it (few of a
+        // large cell's; small cells go through all of theirs). A cut during the
+        // pass leaves the lists good: what cuts the smaller cell cuts the larger.
+        auto below = [&](int at, int n, const Box6 &boxes, int lane, int &met) {
+            met = n;
+            if (C::kTable) return true;
+            met = balls_met(c, at, n, box_f32(lane_box(boxes, lane), p, slack, R.sc));
+            return met > 0;
         };
         auto take = [&](const int32_t *list, int n) {   // up to 64 candidates
             lds_order();
@@ -807,20 +857,21 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
         };
         for (int64_t g2 = 0; g2 < tree.n[2]; g2 += 64) {
             Box6 b2;
-            for (uint64_t h2 = boxes_hit(R, F, all, tree.level[2], tree.n[2], g2, p, from, to, slack, b2); h2; h2 &= h2 - 1) {
+            for (uint64_t h2 = boxes_hit(c, R, 0, n_all, tree.level[2], tree.n[2], g2, p, from, to, slack, b2);
+                 h2; h2 &= h2 - 1) {
                 const int c2 = __ffsll((long long)h2) - 1;
                 const int64_t g1 = (g2 + c2) * 64;
-                VertSet<K> met2;
+                int n2;
                 Box6 b1;
-                if (!below(all, b2, c2, met2)) continue;
-                for (uint64_t h1 = boxes_hit(R, F, met2, tree.level[1], tree.n[1], g1, p, from, to, slack, b1); h1;
+                if (!below(0, n_all, b2, c2, n2)) continue;
+                for (uint64_t h1 = boxes_hit(c, R, 1, n2, tree.level[1], tree.n[1], g1, p, from, to, slack, b1); h1;
                      h1 &= h1 - 1) {
                     const int c1 = __ffsll((long long)h1) - 1;
                     const int64_t g0 = (g1 + c1) * 64;
-                    VertSet<K> met1;
+                    int n1;
                     Box6 b0;
-                    if (!below(met2, b1, c1, met1)) continue;
-                    uint64_t h0 = boxes_hit(R, F, met1, tree.level[0], tree.n[0], g0, p, from, to, slack, b0);
+                    if (!below(1, n2, b1, c1, n1)) continue;
+                    uint64_t h0 = boxes_hit(c, R, 2, n1, tree.level[0], tree.n[0], g0, p, from, to, slack, b0);
                     while (h0) {   // four runs of kLeaf sites per load
                         int leaf[4];
 #pragma unroll
@@ -841,7 +892,7 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
                                     (STRICT || key > near || j < w0 || j >= w0 + 64);
                         uint64_t wm = __ballot(want);
                         if (nbuf + __popcll(wm) > C::kWait) {   // crowded: only those that cut the cell as it stands
-                            const bool cuts = cuts_now(R, dx, dy, dz, 0.5 * d2);   // by every lane
+                            const bool cuts = cuts_now(c, R, dx, dy, dz, 0.5 * d2);
                             want = want && cuts;
                             wm = __ballot(want);
                         }
@@ -862,10 +913,6 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
                             } else {   // too many at one distance: take all that wait now
                                 const int rc = take_waiting();
                                 if (rc < 0) return rc;
-                                stale = true;
-                                F.set(R);
-#pragma unroll
-                                for (int q = 0; q < K; ++q) all.m[q] = R.valid[q];
                             }
                         }
                     }
