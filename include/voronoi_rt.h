@@ -264,7 +264,7 @@ typedef struct {
     int64_t seg_stride;     /* > 0: ray i owns slots [i*seg_stride, (i+1)*seg_stride) */
     const int64_t *ray_off; /* seg_stride == 0: ray i owns [ray_off[i], ray_off[i+1]) */
     unsigned long long *counters; /* [8] accumulated: segments, fallbacks, FP64 re-decisions, steps,
-                                     neighbour records read, wave iterations and refills of the persistent
+                                     neighbour records of the cells stepped through, wave iterations and refills of the persistent
                                      kernel (steps / (64 x iterations) is its lane utilisation), 1 reserved;
                                      may be NULL */
     int64_t *work;          /* [VOR_WORK_WORDS] device control words, required for persistent mode and spill;

@@ -250,6 +250,7 @@ __device__ __forceinline__ void loc_range(const LocArgs &A, int64_t i, int b0[3]
 // (one cell per lane leaves the wave waiting for its largest box: sparse cells
 // next to a dense disc have boxes of thousands of blocks).
 constexpr int kRowLanes = 16;
+constexpr int kExportLds = 256;   // entries of a row held in LDS to order it
 template <class F>
 __device__ __forceinline__ int64_t loc_each(const LocArgs &A, int64_t i, F &&f)
 {
@@ -408,8 +409,10 @@ __global__ void k_row_sort(int32_t *__restrict__ col, const int4 *__restrict__ o
 // every offset component below 2^E (so |q| <= 2^19), but at least e_min, so
 // that the box in the cell's units stays far inside the FP32 range; rounding
 // to the nearest integer leaves each component within half a unit of the
-// scale. FP64 blocks hold the neighbour sites in the row's order (ascending
-// internal index). The neighbours' block offsets follow the records.
+// scale. FP64 blocks hold the neighbour sites. The neighbours' block offsets
+// follow the records. Every row lists its neighbours nearest first (equal
+// distances: the lower index), so that an exit search can stop where the
+// rest are too far away to matter.
 struct FillArgs {
     const Site *sites;
     RowTable rows_in;
@@ -431,6 +434,27 @@ __global__ void __launch_bounds__(256) k_fill_rows(FillArgs A)
     const Site si = A.sites[i];
     const bool compact = A.blk_off != nullptr;
     const int32_t bo = compact ? o.z : block_of(make_int2(o.x, n), (int32_t)i);
+    // squared distances, for the order (rows too long for the LDS: read again)
+    __shared__ double s_d2[256 / kRowLanes][kExportLds];
+    double *d2s = s_d2[threadIdx.x / kRowLanes];
+    const bool held = n <= kExportLds;
+    auto dist2 = [&](int e) {
+        const Site sj = A.sites[row[e]];
+        const double dx = sj.x - si.x, dy = sj.y - si.y, dz = sj.z - si.z;
+        return dx * dx + dy * dy + dz * dz;
+    };
+    if (held)
+        for (int e = li; e < n; e += kRowLanes) d2s[e] = dist2(e);
+    lds_order();
+    auto place = [&](int e) {   // entries before e (the row comes in ascending order of index)
+        const double d = held ? d2s[e] : dist2(e);
+        int r = 0;
+        for (int k = 0; k < n; ++k) {
+            const double dk = held ? d2s[k] : dist2(k);
+            r += (dk < d) | ((dk == d) & (k < e)) ? 1 : 0;
+        }
+        return r;
+    };
     int E = 0;
     if (compact) {
         double mc = 0.0;
@@ -469,10 +493,11 @@ __global__ void __launch_bounds__(256) k_fill_rows(FillArgs A)
     double *rec64 = reinterpret_cast<double *>(A.blk64 + o.y + kHdrSlots);
     int32_t *nb64 = reinterpret_cast<int32_t *>(rec64 + 3 * n);
     const double sc = ldexp(1.0, kQShift - E);
-    for (int e = li; e < n; e += kRowLanes) {
-        const int32_t j = row[e];
+    for (int f = li; f < n; f += kRowLanes) {
+        const int32_t j = row[f];
         const Site sj = A.sites[j];
         const int4 oj = A.rows_in.offs[j];
+        const int e = place(f);
         Rec64 a;
         a.x = sj.x;
         a.y = sj.y;
@@ -513,7 +538,6 @@ __global__ void k_export_counts(const int32_t *__restrict__ inv_perm, const int2
 // Rows of user indices, ascending, then walls: kRowLanes lanes per row, an
 // entry's place being the number of smaller ones in its row (rows too long
 // for their part of the LDS are sorted by their first lane).
-constexpr int kExportLds = 256;
 __global__ void __launch_bounds__(256) k_export_fill(const int32_t *__restrict__ inv_perm, const int2 *__restrict__ rows,
                                                      const Rec64 *__restrict__ r64, const uint8_t *__restrict__ walls,
                                                      int64_t M, const int64_t *__restrict__ row_ptr,

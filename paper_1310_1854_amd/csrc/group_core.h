@@ -111,26 +111,28 @@ __device__ __forceinline__ int32_t cell_block(const GridRef &G, int32_t m)
     return G.blk_off ? G.blk_off[m] : block_of(G.rows[m], m);
 }
 
-// FP64 exit search: site(i) gives record i of the row (called for i < n by
-// the lane that takes it; round r holds records r * W + lane). The winner's
-// place in the row, or -1 when the chord end comes first; the crossing in
-// best. exit_fp64's rules: the smallest crossing below L, then the larger
-// n.k, then the earlier record.
-template <int W, class F>
-__device__ __forceinline__ int group_exit_fp64(F &&site, int n, const double pm[3], const double r0[3],
+// FP64 exit search: site(r, i) gives record i of the row (round r of the
+// lane's own, or later), key(i) a number that grows with the neighbour's
+// internal index. The winner's place in the row, or -1 when the chord end
+// comes first; the crossing in best. exit_fp64's rules: the smallest crossing
+// below L, then the larger n.k, then the lower index.
+template <int W, class F, class K>
+__device__ __forceinline__ int group_exit_fp64(F &&site, K &&key, int n, const double pm[3], const double r0[3],
                                                const double k[3], double L, double &best)
 {
     const int li = threadIdx.x & (W - 1);
     constexpr int32_t kNone = 0x7fffffff;
-    double bs = __builtin_huge_val(), bden = 0.0;
+    double bs = __builtin_huge_val();
     int32_t bi = kNone;
+    bool twice = false;   // this lane has its least crossing more than once
     // (& and | throughout: short-circuits would become branches)
     auto take = [&](int i, const Rec24 &q) {
         double den;
         const double s = cross_fp64(q.x, q.y, q.z, pm, r0, k, den);
-        const bool t = (i < n) & (den > 0.0) & (s < L) & ((bi == kNone) | (s < bs) | ((s == bs) & (den > bden)));
+        const bool ok = (i < n) & (den > 0.0) & (s < L);
+        const bool t = ok & ((bi == kNone) | (s < bs));
+        twice = t ? false : twice | (ok & (s == bs));
         bs = t ? s : bs;
-        bden = t ? den : bden;
         bi = t ? i : bi;
     };
 #pragma unroll
@@ -140,14 +142,29 @@ __device__ __forceinline__ int group_exit_fp64(F &&site, int n, const double pm[
     group_exchange<W>([&](auto x) { least = fmin(least, x.f64(least)); });
     const bool own = (bi != kNone) & (bs == least);
     const uint32_t owners = group_bits<W>(__ballot(own));
-    if (__ballot((owners & (owners - 1u)) != 0u)) {   // some group has equal crossings
-        bden = own ? bden : -1.0;
-        bi = own ? bi : kNone;
+    const bool tied = ((owners & (owners - 1u)) != 0u) | (group_bits<W>(__ballot(own & twice)) != 0u);
+    if (__ballot(tied)) {   // some group has equal crossings: all of them again, with the other rules
+        double bden = -1.0;
+        int32_t bk = kNone;
+        bi = kNone;
+        for (int i = li, r = 0; i < n; i += W, ++r) {
+            double den;
+            const Rec24 q = site(kGroupRounds, i);
+            const double s = cross_fp64(q.x, q.y, q.z, pm, r0, k, den);
+            if (!(den > 0.0) || s != least) continue;
+            const int32_t ki = key(i);
+            if (den > bden || (den == bden && ki < bk)) {
+                bden = den;
+                bk = ki;
+                bi = i;
+            }
+        }
         group_exchange<W>([&](auto x) {
             const double od = x.f64(bden);
-            const int32_t oi = x.i32(bi);
-            const bool t = (od > bden) | ((od == bden) & (oi < bi));
+            const int32_t ok = x.i32(bk), oi = x.i32(bi);
+            const bool t = (od > bden) | ((od == bden) & (ok < bk));
             bden = t ? od : bden;
+            bk = t ? ok : bk;
             bi = t ? oi : bi;
         });
     } else {
@@ -338,21 +355,22 @@ __device__ __forceinline__ void group_walk(const GridRef &G, const RayIn &I, con
             const Rec24 *rec = reinterpret_cast<const Rec24 *>(G.blk64 + C.b + kHdrSlots);
             w = group_exit_fp64<W>(
                 [&](int r, int i) {
-                    return r < kGroupRounds ? Rec24{C.d[r][0], C.d[r][1], C.d[r][2]} : rec[i];
+                    if (r >= kGroupRounds) return rec[i];
+                    return Rec24{C.d[r][0], C.d[r][1], C.d[r][2]};
                 },
-                C.n, C.pm, R.r0, R.k, R.L, best);
+                [&](int i) { return off[i]; }, C.n, C.pm, R.r0, R.k, R.L, best);
         } else {
             bool redo;
             w = group_exit_mixed<MODE, W>(G, C, R.r0, R.k, R.L, R.s_c, redo);
             if (redo) {
                 ++S.nredo;
-                const Rec64 *rec = G.rec64 + C.row;
+                const Rec64 *rec = G.rec64 + C.row;   // in the order of the block's records
                 w = group_exit_fp64<W>(
                     [&](int, int i) {
                         const Rec64 q = rec[i < C.n ? i : 0];
                         return Rec24{q.x, q.y, q.z};
                     },
-                    C.n, C.pm, R.r0, R.k, R.L, best);
+                    [&](int i) { return rec[i].j; }, C.n, C.pm, R.r0, R.k, R.L, best);
             }
         }
         GroupCell<MODE> N;

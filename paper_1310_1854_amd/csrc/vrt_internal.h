@@ -29,10 +29,10 @@ struct __align__(16) Slot {
 // Cell blocks of the mixed-precision search, one per cell in internal
 // order, in 16-byte slots: a header of kHdrSlots slots, then the cell's row
 // of n neighbours as n FP32 records of 12 bytes (the offset p_j - p_m
-// rounded to FP32), then the n block offsets of those neighbours (int32):
+// rounded to FP32; nearest first), then the n block offsets of those neighbours (int32):
 // 48 + 16 n bytes, so the block of cell j starts at slot
-// rows[j].x + kHdrSlots * j. The search reads the records only (8 of them
-// are 6 aligned 16-byte loads) and the block offset of the winner alone.
+// rows[j].x + kHdrSlots * j. The search reads the records only (4 of them
+// are 3 aligned 16-byte loads) and the block offset of the winner alone.
 // What a step needs of the cell it moves into (its FP64 site, indices, row
 // and bound density) lies in the lines of its first records.
 // A grid may instead use compact blocks (Grid::compact): the same header,
