@@ -43,7 +43,8 @@ HBM_PEAK_GBS = 8000.0
 # The sources the trace kernel is compiled from: a traffic figure measured
 # on another version of them is not reported.
 KERNEL_SOURCES = ("paper_1310_1854_amd/csrc/trace.hip", "paper_1310_1854_amd/csrc/trace_core.h",
-                  "paper_1310_1854_amd/csrc/locate_core.h",
+                  "paper_1310_1854_amd/csrc/locate_core.h", "paper_1310_1854_amd/csrc/group_core.h",
+                  "paper_1310_1854_amd/csrc/lanes.h",
                   "paper_1310_1854_amd/csrc/vrt_internal.h", "include/voronoi_rt.h",
                   "paper_1310_1854_amd/build_lib.py")
 # Counter summaries of the trace kernel per workload (profiles/).

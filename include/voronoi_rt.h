@@ -135,9 +135,9 @@ typedef struct {
  * the sites and derives each site's neighbour list. The neighbours of site i
  * are found by clipping the box with the bisector half-spaces of nearby
  * sites (Sect. 2.1: a cell is the set of points at least as close to its
- * site as to any other); candidates come from a uniform bucket grid in
- * rings of increasing distance and the search stops when no farther site
- * can cut the cell. Lists are symmetric and may hold degenerate contacts
+ * site as to any other); candidates come from a tree of bounding boxes over
+ * the sites in Hilbert order, and every site that could still cut the cell
+ * is tried. Lists are symmetric and may hold degenerate contacts
  * (an edge or vertex shared with a cell), which never change a path.
  *   sites  device, M x 3, user order; read during the call only.
  *   M      number of sites, >= 1 and < 2^31.
@@ -208,8 +208,10 @@ vor_status vor_grid_neighbors(const vor_grid *grid, int64_t *row_ptr, int32_t *c
  * vor_locate -- the function C(r) of Sect. 2.3: for each point the index of
  * the cell containing it, i.e. of the nearest site (squared distances; equal
  * distances go to the lowest index), or -1 for a point outside the closed box
- * (step 1 there). Candidate sites come from the bucket grid in rings of
- * increasing distance until no farther bucket can hold a nearer site.
+ * (step 1 there). The search walks from a nearby site to the neighbour
+ * nearest to the point until none is nearer; where rounding leaves that in
+ * doubt it is done over in rings of buckets of sites, until no farther bucket
+ * can hold a nearer site.
  *   pts   device, N x 3.     cell  device, N int32.    N >= 0.
  * Asynchronous on `stream`; allocates nothing.
  */

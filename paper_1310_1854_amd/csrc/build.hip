@@ -9,8 +9,9 @@
 //     than twice the cell's largest vertex radius, found through a tree of
 //     bounding boxes over that order; the planes left bounding the cell are
 //     its neighbours (Sect. 2.1);
-//  5. make the lists symmetric, sort each row, and lay out the trace
-//     records (FP64 sites and FP32 offsets per neighbour, CSR by cell).
+//  5. make the lists symmetric, order each row nearest neighbour first, and
+//     lay out the trace records (FP64 sites and FP32 offsets per neighbour,
+//     CSR by cell).
 #include <chrono>
 #include <cmath>
 #include <cstring>
