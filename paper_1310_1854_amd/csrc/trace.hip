@@ -623,7 +623,22 @@ vor_status launch_trace_ext(const TraceArgs &A, bool persistent, int cus, hipStr
         hipLaunchKernelGGL(k_start_cells, dim3((unsigned)((A.N + T - 1) / T)), dim3(T), 0, st, A);
     if (persistent) {
         static const int per_cu = resident_blocks_per_cu(k_trace_persistent<MODE, SEGS, EXT>);
-        const int64_t blocks = std::min<int64_t>((int64_t)cus * per_cu, (A.N + T - 1) / T);
+        // How many of the blocks that fit are launched: with few rays per lane
+        // more waves only mean shorter queues and more idle lanes at the end,
+        // and FP64's fourth block per unit costs more in L2 misses than it
+        // hides. Whole calls (us) with 2 / 3 / 4 blocks per unit:
+        //   exp. disc     300000 FP64   2062/2169/2264    mixed 1551/1688
+        //   flared disc   450000        4621/5051/5588          2793/3159
+        //                 600000        5698/5666/6294          3510/3337
+        //                10^6           8580/8073/8604          5202/4732
+        //               8x10^6         56543/49508/49243       34884/29989
+        //   clumpy       4x10^6         54395/57271/61323       34272/29309
+        // and without segments, where the fourth block pays on long queues:
+        //   flared disc  10^6           7182/6647/7247          4352/3785/3965
+        //               4x10^6         24730/21408/21330       14877/12374/12136
+        const int64_t turn = (int64_t)cus * T;
+        const int most = A.N < 8 * turn ? 2 : SEGS || A.N < 48 * turn ? 3 : 4;
+        const int64_t blocks = std::min<int64_t>((int64_t)cus * std::min(per_cu, most), (A.N + T - 1) / T);
         hipLaunchKernelGGL((k_trace_persistent<MODE, SEGS, EXT>), dim3((unsigned)std::max<int64_t>(blocks, 1)),
                            dim3(T), 0, st, A);
     } else {
