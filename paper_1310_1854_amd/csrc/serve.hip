@@ -85,9 +85,10 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Every ray of chunk slot's request chunk has been written by this wave:
-// make the writes visible device-wide (a release fence: the wave's L2
-// writes back, nothing is invalidated), count the chunk off its request,
+// Every ray of a chunk of request q has been written, by this wave or by
+// waves of its block that waited for their stores first: make the writes
+// visible device-wide (a release fence: the wave's L2 writes back, nothing is
+// invalidated), count the chunk off its request,
 // and the wave that completes the request's last chunk -- after an acquire
 // fence, once per request -- raises its flag in host memory (release at
 // system scope, so the flag is seen after the data): 1 when every path is
@@ -380,6 +381,10 @@ __global__ void __launch_bounds__(256) k_serve_group(const GridRef *__restrict__
             if (S.nredo) atomicAdd(&sum[2], (unsigned long long)S.nredo);
         }
     }
+    // Each wave waits for its own stores and overflow counts: the last one's
+    // release waits for those of its own wave only, and the count in LDS for
+    // none (a workgroup-scope release does not wait for global stores).
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     int at = 0;
     if ((threadIdx.x & 63) == 0) at = __hip_atomic_fetch_add(&ended, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (__shfl(at, 0, 64) == 3) {   // the block's last wave
