@@ -85,10 +85,15 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// Waits until this wave's vector stores and atomics have reached the L2. (The
+// compiler drops the wait of a release fence where it knows of no store in
+// flight, also behind the write-back that the fence starts.)
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Every ray of a chunk of request q has been written, by this wave or by
-// waves of its block that waited for their stores first: make the writes
-// visible device-wide (a release fence: the wave's L2 writes back, nothing is
-// invalidated), count the chunk off its request,
+// waves of its block that waited for their stores first (they share its L2):
+// make the writes visible device-wide (a release fence: the wave's L2 writes
+// back, nothing is invalidated), count the chunk off its request,
 // and the wave that completes the request's last chunk -- after an acquire
 // fence, once per request -- raises its flag in host memory (release at
 // system scope, so the flag is seen after the data): 1 when every path is
@@ -101,6 +106,7 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 __device__ __forceinline__ void chunk_complete(const ReqDev *__restrict__ reqs, int q)
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    wait_stores();
     if ((threadIdx.x & 63) == 0) {
         const int prev = __hip_atomic_fetch_add(reqs[q].remaining, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (prev == 1) {
@@ -383,8 +389,10 @@ __global__ void __launch_bounds__(256) k_serve_group(const GridRef *__restrict__
     }
     // Each wave waits for its own stores and overflow counts: the last one's
     // release waits for those of its own wave only, and the count in LDS for
-    // none (a workgroup-scope release does not wait for global stores).
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    // none (a workgroup-scope release does not wait for global stores). With a
+    // release of its own, and so a write-back of the L2, in each wave: 12
+    // requests of 256 to 65536 rays 4.98 ms; with this wait 4.34 ms.
+    wait_stores();
     int at = 0;
     if ((threadIdx.x & 63) == 0) at = __hip_atomic_fetch_add(&ended, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (__shfl(at, 0, 64) == 3) {   // the block's last wave
