@@ -147,7 +147,7 @@ struct ClipArgs {
     uint8_t *walls;           // [M]
     int32_t *retry;           // [M] sites whose cell needs the large capacity
     int32_t *n_retry;
-    int32_t *touched;         // [M] sites whose cell asks for the strict order
+    int32_t *touched;         // [M] sites whose cell goes to the strict order
     int32_t *n_touched;
     int *err;
     double *volume;           // [M] cell volumes
@@ -173,8 +173,9 @@ __device__ __forceinline__ void clip_result(const ClipArgs &A, int64_t i, int n,
 }
 
 // First pass: one wave per site with a small cell; cells that run out of
-// vertices are queued for the large capacity, cells in which a cut passed
-// through a vertex (lattices) for the strict order. The grid is a multiple
+// vertices are queued for the large capacity, cells in which a cut passes
+// through a vertex (lattices), or which degenerate (no vertex is left, or a
+// new one is not finite), for the strict order. The grid is a multiple
 // of kXcds blocks: block b runs on XCD b mod kXcds, and each XCD takes one
 // contiguous part of the Hilbert order, so that its L2 holds the sites
 // around it.
@@ -186,8 +187,9 @@ __global__ void __launch_bounds__(64) k_clip(ClipArgs A)
     if (i >= A.M) return;
     uint32_t walls = 0;
     double vol = 0.0;
-    const int n = wclip_site<WaveCellSmall, false>(cell, A.sites, A.M, A.tree, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr,
-                                                   walls, vol, A.bbox ? A.bbox + 6 * i : nullptr);
+    int n = wclip_site<WaveCellSmall, false>(cell, A.sites, A.M, A.tree, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr, walls,
+                                             vol, A.bbox ? A.bbox + 6 * i : nullptr);
+    if (n == -ERR_DEGENERATE) n = -ERR_TOUCH;
     if (threadIdx.x == 0) clip_result(A, i, n, walls, vol);
 }
 

@@ -111,7 +111,7 @@ struct LaneVerts {
     double sr;              // its square root
     double sc;              // wave-uniform: a power of two that scales the box to about 1, for FP32
     int np;                 // wave-uniform: plane slots in use
-    bool touch;             // wave-uniform: a cut passed through a vertex, to within its tolerance
+    bool loose;             // wave-uniform: the planes do not come strictly nearest first
 };
 
 __device__ __forceinline__ uint32_t wpack3(int a, int b, int c)
@@ -261,13 +261,13 @@ __device__ __forceinline__ void wcell_init(C &c, LaneVerts<C::kPerLane> &R, cons
         set_ball(c, R, l, R.x[0], R.y[0], R.z[0]);
     }
     R.np = 6;
-    R.touch = false;
     update_r2(R);
     lds_order();
 }
 
 // Cut the cell by {v : n.v <= d} (plane id `id`, all wave-uniform). Returns
-// 1, 0 when the plane cuts nothing off, or an -ERR_* code.
+// 1, 0 when the plane cuts nothing off, or an -ERR_* code: in the loose order
+// ERR_TOUCH when the cut passes through a vertex, to within its tolerance.
 template <class C>
 __device__ __forceinline__ int wcell_cut(C &c, LaneVerts<C::kPerLane> &R, double nx, double ny, double nz, double d,
                                          int32_t id)
@@ -287,7 +287,7 @@ __device__ __forceinline__ int wcell_cut(C &c, LaneVerts<C::kPerLane> &R, double
         kept |= R.valid[q] & ~off[q];
     }
     if (any == 0) return 0;
-    R.touch = R.touch || on != 0;
+    if (R.loose && on != 0) return -ERR_TOUCH;
     if (kept == 0) return -ERR_DEGENERATE;   // the site itself is always strictly inside
     // plane slot of the new face: a fresh one, or one no kept vertex uses
     int Pn = R.np;
@@ -759,8 +759,8 @@ __device__ __forceinline__ void wcell_bbox(const LaneVerts<K> &R, const double p
 // mask and the volume go to the caller's variables. Returns the count or
 // -ERR_*. All lanes of the wave call it with the same i. STRICT takes every
 // site nearest first, without the Hilbert neighbourhood's head start;
-// otherwise a cell in which a cut passed through a vertex is refused with
-// ERR_TOUCH.
+// otherwise (with more than 64 sites) the order is loose, and a cell in which
+// a cut passes through a vertex is refused with ERR_TOUCH.
 template <class C, bool STRICT>
 __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, int64_t M, const BoxTree &tree,
                                           const BoxArg &box, int64_t i, int32_t *nbr, int max_nbr, uint32_t &walls,
@@ -774,6 +774,7 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
     double slack = 0.0;   // rounding of box coordinates
     for (int a = 0; a < 3; ++a) slack = fmax(slack, 1e-15 * fmax(fabs(box.lo[a]), fabs(box.hi[a])));
     LaneVerts<K> R;
+    R.loose = !STRICT && M > 64;
     wcell_init(c, R, p, box);
     // the nearer half of the neighbourhood in Hilbert order (of up to 64 sites: everything)
     const int64_t w0 = max((int64_t)0, min(i - 32, M - 64));
@@ -929,7 +930,6 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
         from = to;
         to = next;
     }
-    if (!STRICT && R.touch && M > 64) return -ERR_TOUCH;
     volume = wcell_volume(c, R);
     if (bbox) wcell_bbox(R, p, bbox);
     // faces: plane slots some vertex still uses
