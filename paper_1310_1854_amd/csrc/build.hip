@@ -149,6 +149,8 @@ struct ClipArgs {
     int32_t *n_retry;
     int32_t *touched;         // [M] sites whose cell goes to the strict order
     int32_t *n_touched;
+    int32_t *open;            // [M] sites whose cell came out of the strict order as no polyhedron
+    int32_t *n_open;
     int *err;
     double *volume;           // [M] cell volumes
     double *bbox;             // [6 M] cell bounding boxes, or null
@@ -164,6 +166,9 @@ __device__ __forceinline__ void clip_result(const ClipArgs &A, int64_t i, int n,
     } else if (n == -ERR_TOUCH) {
         A.touched[atomicAdd(A.n_touched, 1)] = (int32_t)i;
         n = 0;
+    } else if (n == -ERR_OPEN) {
+        A.open[atomicAdd(A.n_open, 1)] = (int32_t)i;
+        n = 0;
     } else if (n < 0) {
         atomicOr(A.err, -n);
         n = 0;
@@ -174,11 +179,11 @@ __device__ __forceinline__ void clip_result(const ClipArgs &A, int64_t i, int n,
 
 // First pass: one wave per site with a small cell; cells that run out of
 // vertices are queued for the large capacity, cells in which a cut passes
-// through a vertex (lattices), or which degenerate (no vertex is left, or a
-// new one is not finite), for the strict order. The grid is a multiple
-// of kXcds blocks: block b runs on XCD b mod kXcds, and each XCD takes one
-// contiguous part of the Hilbert order, so that its L2 holds the sites
-// around it.
+// through a vertex (lattices), or which degenerate (no vertex is left, a new
+// one is not finite, or they bound no polyhedron), for the strict order. The
+// grid is a multiple of kXcds blocks: block b runs on XCD b mod kXcds, and each
+// XCD takes one contiguous part of the Hilbert order, so that its L2 holds the
+// sites around it.
 constexpr int kXcds = 8;
 __global__ void __launch_bounds__(64) k_clip(ClipArgs A)
 {
@@ -188,8 +193,8 @@ __global__ void __launch_bounds__(64) k_clip(ClipArgs A)
     uint32_t walls = 0;
     double vol = 0.0;
     int n = wclip_site<WaveCellSmall, false>(cell, A.sites, A.M, A.tree, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr, walls,
-                                             vol, A.bbox ? A.bbox + 6 * i : nullptr);
-    if (n == -ERR_DEGENERATE) n = -ERR_TOUCH;
+                                             vol, A.bbox ? A.bbox + 6 * i : nullptr, kCutTol, false);
+    if (n == -ERR_DEGENERATE || n == -ERR_OPEN) n = -ERR_TOUCH;
     if (threadIdx.x == 0) clip_result(A, i, n, walls, vol);
 }
 
@@ -200,8 +205,22 @@ __global__ void __launch_bounds__(64) k_clip_strict(ClipArgs A)
     const int64_t i = A.touched[blockIdx.x];
     uint32_t walls = 0;
     double vol = 0.0;
-    const int n = wclip_site<WaveCellSmall, true>(cell, A.sites, A.M, A.tree, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr,
-                                                  walls, vol, A.bbox ? A.bbox + 6 * i : nullptr);
+    int n = wclip_site<WaveCellSmall, true>(cell, A.sites, A.M, A.tree, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr, walls, vol,
+                                            A.bbox ? A.bbox + 6 * i : nullptr, kCutTol, false);
+    if (n == -ERR_DEGENERATE) n = -ERR_OPEN;
+    if (threadIdx.x == 0) clip_result(A, i, n, walls, vol);
+}
+
+// Those that came out as no polyhedron, with other tolerances (in a kernel of
+// its own: the loop costs two of five waves per SIMD).
+__global__ void __launch_bounds__(64) k_clip_open(ClipArgs A)
+{
+    __shared__ WaveCellSmall cell;
+    const int64_t i = A.open[blockIdx.x];
+    uint32_t walls = 0;
+    double vol = 0.0;
+    const int n = strict_site(cell, A.sites, A.M, A.tree, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr, walls, vol,
+                              A.bbox ? A.bbox + 6 * i : nullptr, 1);
     if (threadIdx.x == 0) clip_result(A, i, n, walls, vol);
 }
 
@@ -213,8 +232,8 @@ __global__ void __launch_bounds__(64) k_clip_big(ClipArgs A, int32_t *__restrict
     const int64_t i = A.retry[k];
     uint32_t wm = 0;
     double vol = 0.0;
-    int n = wclip_site<WaveCellBig, true>(cell, A.sites, A.M, A.tree, A.box, i, big_nbr + (int64_t)k * kMaxNbrBig,
-                                          kMaxNbrBig, wm, vol, A.bbox ? A.bbox + 6 * i : nullptr);
+    int n = strict_site(cell, A.sites, A.M, A.tree, A.box, i, big_nbr + (int64_t)k * kMaxNbrBig, kMaxNbrBig, wm, vol,
+                        A.bbox ? A.bbox + 6 * i : nullptr, 0);
     if (threadIdx.x == 0) {
         A.volume[i] = vol;
         slot[i] = k;
@@ -763,7 +782,7 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     }
     uint32_t *keys, *keys2;
     int32_t *vals, *vals2, *hist, *bcount, *nbr0, *cnt0, *retry, *slot, *extra, *lcnt = nullptr;
-    int *err;   // error flags, -, sites to retry, touched, longest row, missing entries
+    int *err;   // error flags, -, sites to retry, touched, longest row, missing entries, open
     int4 *sizes, *offs;
     unsigned long long *ltot = nullptr;
     BoxTree tree;   // boxes over runs of kLeaf sites, then over 64 boxes each
@@ -852,25 +871,30 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     ca.n_retry = err + 2;
     ca.touched = extra;   // filled again for the rows
     ca.n_touched = err + 3;
+    ca.open = vals2;      // (the sorts are done)
+    ca.n_open = err + 6;
     ca.err = err;
     ca.volume = g.volume;
     ca.bbox = g.bbox;
     if (hipMemsetAsync(slot, 0xff, sizeof(int32_t) * M, st) != hipSuccess) return fail(VOR_EDEVICE);
     hipLaunchKernelGGL(k_clip, dim3((unsigned)(kXcds * ((M + kXcds - 1) / kXcds))), dim3(64), 0, st, ca);
     if (hipGetLastError() != hipSuccess) return fail(VOR_EDEVICE);
-    int hflags[4] = {0, 0, 0, 0};
-    if (hipMemcpyAsync(hflags, err, 4 * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return fail(VOR_EDEVICE);
-    if (hflags[0] & ERR_DUP) return fail(VOR_EDUP);
-    if (hflags[0] & (ERR_CAPACITY | ERR_DEGENERATE)) return fail(VOR_ECAPACITY);
+    int hflags[7] = {0, 0, 0, 0, 0, 0, 0};
+    auto clipped = [&]() {   // the counts so far, or why the build has failed
+        if (hipMemcpyAsync(hflags, err, sizeof(hflags), hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess)
+            return VOR_EDEVICE;
+        if (hflags[0] & ERR_DUP) return VOR_EDUP;
+        return hflags[0] & (ERR_CAPACITY | ERR_DEGENERATE) ? VOR_ECAPACITY : VOR_OK;
+    };
+    if ((rc = clipped()) != VOR_OK) return fail(rc);
     if (hflags[3] > 0) {
         hipLaunchKernelGGL(k_clip_strict, dim3((unsigned)hflags[3]), dim3(64), 0, st, ca);
-        if (hipMemcpyAsync(hflags, err, 4 * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess)
-            return fail(VOR_EDEVICE);
-        if (hflags[0] & ERR_DUP) return fail(VOR_EDUP);
-        if (hflags[0] & (ERR_CAPACITY | ERR_DEGENERATE)) return fail(VOR_ECAPACITY);
+        if ((rc = clipped()) != VOR_OK) return fail(rc);
+    }
+    if (hflags[6] > 0) {
+        hipLaunchKernelGGL(k_clip_open, dim3((unsigned)hflags[6]), dim3(64), 0, st, ca);
+        if ((rc = clipped()) != VOR_OK) return fail(rc);
     }
     const int n_retry = hflags[2];
     int32_t *big_nbr = nullptr;
@@ -879,11 +903,7 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
         more.add(big_nbr, (size_t)n_retry * kMaxNbrBig);
         if (!more.alloc(tmp, A)) return fail(VOR_ENOMEM);
         hipLaunchKernelGGL(k_clip_big, dim3((unsigned)n_retry), dim3(64), 0, st, ca, big_nbr, slot);
-        if (hipMemcpyAsync(hflags, err, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess)
-            return fail(VOR_EDEVICE);
-        if (hflags[0] & ERR_DUP) return fail(VOR_EDUP);
-        if (hflags[0] & (ERR_CAPACITY | ERR_DEGENERATE)) return fail(VOR_ECAPACITY);
+        if ((rc = clipped()) != VOR_OK) return fail(rc);
     }
     g.n_big = n_retry;
 

@@ -27,11 +27,19 @@
 // an edge or a vertex leave no sliver face -- provided that they come after
 // the planes they meet there, so a cell in which a cut passes through a
 // vertex is clipped again strictly nearest first, as lattices need). The
-// vertices kept stay where they are. The rim of the cut (edges of removed vertices whose twin edge is
-// kept) comes from a table of the vertex that holds each directed edge, one
-// LDS read per edge; the new vertices go to free lanes and write their edges
-// there. (Small cells only; a table for 255 planes would fill the LDS, so
-// large cells compare the removed vertices pairwise.)
+// vertices kept stay where they are. The rim of the cut (edges of removed
+// vertices whose twin edge is kept) comes from a table of the vertex that
+// holds each directed edge, one LDS read per edge; the new vertices go to free
+// lanes and write their edges there. (Small cells only; a table for 255 planes
+// would fill the LDS, so large cells compare the removed vertices pairwise.)
+//
+// Where the vertices of many planes fall together (sites on a sphere or a
+// circle: every bisector goes through its centre), their rounding may exceed
+// the tolerance; the vertices a cut removes are then no connected part of the
+// boundary, its rim is no single cycle, and what is left is no polyhedron. The
+// edges, which no longer come in pairs, and Euler's relation (V = 2 F - 4 for
+// a simple polyhedron) show that at the end, and the cell is clipped again
+// with another tolerance: see strict_site.
 //
 // What bounds it: instruction issue, with 4 to 5 waves per SIMD to hide the
 // LDS round trips. About 22 cuts of some 220 instructions per cell are more
@@ -50,7 +58,7 @@ namespace vrt {
 
 constexpr int kHilbertBits = 10;   // per axis
 
-enum : int { ERR_OUTSIDE = 1, ERR_DUP = 2, ERR_CAPACITY = 4, ERR_DEGENERATE = 8, ERR_TOUCH = 16 };
+enum : int { ERR_OUTSIDE = 1, ERR_DUP = 2, ERR_CAPACITY = 4, ERR_DEGENERATE = 8, ERR_TOUCH = 16, ERR_OPEN = 32 };
 
 struct BoxArg {
     double lo[3], hi[3];
@@ -111,6 +119,7 @@ struct LaneVerts {
     double sr;              // its square root
     double sc;              // wave-uniform: a power of two that scales the box to about 1, for FP32
     int np;                 // wave-uniform: plane slots in use
+    double tol;             // wave-uniform: relative tolerance of the cuts
     bool loose;             // wave-uniform: the planes do not come strictly nearest first
 };
 
@@ -276,7 +285,7 @@ __device__ __forceinline__ int wcell_cut(C &c, LaneVerts<C::kPerLane> &R, double
     const int l = lane_id();
     const uint64_t lt = lanemask_lt();
     // relative tolerance: the scale of the terms of n.v - d (d = |n|^2 / 2)
-    const double tol = 1e-12 * (__builtin_amdgcn_sqrt(2.0 * d) * R.sr + d);
+    const double tol = R.tol * (__builtin_amdgcn_sqrt(2.0 * d) * R.sr + d);
     uint64_t off[K], any = 0, kept = 0, on = 0;
 #pragma unroll
     for (int q = 0; q < K; ++q) {
@@ -660,6 +669,13 @@ __device__ __forceinline__ int drop_waiting(C &c, int n, uint32_t k1)
     return kept;
 }
 
+// Whether x -> y is an edge of the vertex of planes w.
+__device__ __forceinline__ bool has_edge(uint32_t w, int x, int y)
+{
+    const int a = w & 255, b = (w >> 8) & 255, c = (w >> 16) & 255;
+    return ((a == x) & (b == y)) | ((b == x) & (c == y)) | ((c == x) & (a == y));
+}
+
 // Volume of the clipped cell, by the whole wave. The cell is the union of
 // the cones from the site (the origin here) to its faces, so
 // V = sum over faces x of (h_x / 3) * area_x, with h_x = d_x / |n_x| the
@@ -668,12 +684,14 @@ __device__ __forceinline__ int drop_waiting(C &c, int n, uint32_t k1)
 // holding the reversed edge (y, x), the other end of the polyhedron edge
 // between faces x and y; so 2 area_x = |sum over the face's vertices of
 // n_x / |n_x| . (v_t x v_next)|, with one orientation for every face.
+// closed: every edge (x, y) is one vertex's, and its reverse one vertex's.
 template <class C>
-__device__ __forceinline__ double wcell_volume(C &c, const LaneVerts<C::kPerLane> &R)
+__device__ __forceinline__ double wcell_volume(C &c, const LaneVerts<C::kPerLane> &R, bool &closed)
 {
     constexpr int K = C::kPerLane, P = C::kPlanes;
     const int l = lane_id();
     double acc = 0.0;
+    bool apart = false;
     int nt = 0;
     if constexpr (!C::kTable) {   // all vertices in LDS
         for (int q = 0; q < K; ++q) {
@@ -704,6 +722,9 @@ __device__ __forceinline__ double wcell_volume(C &c, const LaneVerts<C::kPerLane
         for (int e = 0; e < 3; ++e) {
             const int x = corner[e], y = corner[(e + 1) % 3];
             const int t2 = have ? c.twin[y * P + x] & 63 : l;
+            const uint32_t w = __shfl(u, t2, 64);   // (of a vertex no longer there: what it was)
+            const bool there = (R.valid[0] >> t2) & 1ull;
+            apart |= have & (!there | !has_edge(w, y, x) | (c.twin[x * P + y] != l));
             const double ux = __shfl(R.x[0], t2, 64), uy = __shfl(R.y[0], t2, 64), uz = __shfl(R.z[0], t2, 64);
             if (have) cone(x, R.x[0], R.y[0], R.z[0], ux, uy, uz);
         }
@@ -714,16 +735,21 @@ __device__ __forceinline__ double wcell_volume(C &c, const LaneVerts<C::kPerLane
             for (int e = 0; e < 3; ++e) {
                 const int x = corner[e], y = corner[(e + 1) % 3];
                 int t2 = -1;
-                for (int s = 0; s < nt && t2 < 0; ++s) {
+                for (int s = 0; s < nt; ++s) {
                     const uint32_t w = c.list[s];
-                    const int a = w & 255, b = (w >> 8) & 255, cc = (w >> 16) & 255;
-                    if ((a == y && b == x) || (b == y && cc == x) || (cc == y && a == x)) t2 = s;
+                    apart |= has_edge(w, x, y) & (s != t);
+                    if (has_edge(w, y, x)) {
+                        apart |= t2 >= 0;
+                        t2 = t2 < 0 ? s : t2;
+                    }
                 }
-                if (t2 < 0) continue;   // cannot happen in a closed cell
+                apart |= t2 < 0;
+                if (t2 < 0) continue;
                 cone(x, c.v[3 * t], c.v[3 * t + 1], c.v[3 * t + 2], c.v[3 * t2], c.v[3 * t2 + 1], c.v[3 * t2 + 2]);
             }
         }
     }
+    closed = __ballot(apart) == 0;
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     return fabs(acc) / 6.0;
 }
@@ -760,11 +786,13 @@ __device__ __forceinline__ void wcell_bbox(const LaneVerts<K> &R, const double p
 // -ERR_*. All lanes of the wave call it with the same i. STRICT takes every
 // site nearest first, without the Hilbert neighbourhood's head start;
 // otherwise (with more than 64 sites) the order is loose, and a cell in which
-// a cut passes through a vertex is refused with ERR_TOUCH.
+// a cut passes through a vertex is refused with ERR_TOUCH. tol is the relative
+// tolerance of the cuts; a cell that is no closed polyhedron at the end is
+// refused with ERR_OPEN unless `open` lets it pass.
 template <class C, bool STRICT>
 __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, int64_t M, const BoxTree &tree,
                                           const BoxArg &box, int64_t i, int32_t *nbr, int max_nbr, uint32_t &walls,
-                                          double &volume, double *bbox)
+                                          double &volume, double *bbox, double tol, bool open)
 {
     constexpr int K = C::kPerLane, P = C::kPlanes;
     const int l = lane_id();
@@ -774,6 +802,7 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
     double slack = 0.0;   // rounding of box coordinates
     for (int a = 0; a < 3; ++a) slack = fmax(slack, 1e-15 * fmax(fabs(box.lo[a]), fabs(box.hi[a])));
     LaneVerts<K> R;
+    R.tol = tol;
     R.loose = !STRICT && M > 64;
     wcell_init(c, R, p, box);
     // the nearer half of the neighbourhood in Hilbert order (of up to 64 sites: everything)
@@ -930,31 +959,40 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
         from = to;
         to = next;
     }
-    volume = wcell_volume(c, R);
-    if (bbox) wcell_bbox(R, p, bbox);
     // faces: plane slots some vertex still uses
     constexpr int W = (P + 63) / 64;
-    uint64_t used[W];
+    uint64_t face[W];
+    int faces = 0, verts = 0;
 #pragma unroll
-    for (int w = 0; w < W; ++w) used[w] = 0;
+    for (int w = 0; w < W; ++w) face[w] = 0;
 #pragma unroll
-    for (int q = 0; q < K; ++q)
+    for (int q = 0; q < K; ++q) {
+        verts += __popcll(R.valid[q]);
         if ((R.valid[q] >> l) & 1ull) {
             const uint32_t u = R.tri[q];
             const int v0 = u & 255, v1 = (u >> 8) & 255, v2 = (u >> 16) & 255;
 #pragma unroll
             for (int w = 0; w < W; ++w)
-                used[w] |= ((v0 >> 6) == w ? 1ull << (v0 & 63) : 0ull) | ((v1 >> 6) == w ? 1ull << (v1 & 63) : 0ull) |
+                face[w] |= ((v0 >> 6) == w ? 1ull << (v0 & 63) : 0ull) | ((v1 >> 6) == w ? 1ull << (v1 & 63) : 0ull) |
                            ((v2 >> 6) == w ? 1ull << (v2 & 63) : 0ull);
         }
+    }
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        face[w] = wave_or_u64(face[w]);
+        faces += __popcll(face[w]);
+    }
+    bool closed;
+    volume = wcell_volume(c, R, closed);
+    if (!open && (!closed || verts != 2 * faces - 4)) return -ERR_OPEN;
+    if (bbox) wcell_bbox(R, p, bbox);
     int nn = 0;
     walls = 0;
     lds_order();
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-        const uint64_t face = wave_or_u64(used[w]);
         const int s = w * 64 + l;
-        const bool is = (face >> l) & 1ull;
+        const bool is = (face[w] >> l) & 1ull;
         const int32_t id = is ? c.id[s] : 0;
         const uint64_t bal = __ballot(is && id >= 0);
         if (is && id >= 0) c.buf[nn + __popcll(bal & lt)] = id;
@@ -971,6 +1009,28 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
         nbr[r] = id;
     }
     return nn;
+}
+
+// Clip site i's cell with the planes strictly nearest first (wclip_site's
+// results). A cell that degenerates or is no polyhedron with one tolerance is
+// taken again with the next, the wider ones first (a smaller one first took two
+// to four tries each where 1e-11 nearly always does); where none of them helps,
+// as it comes out with the one of all cells. Of the cells of 1000 sites on a
+// sphere 4 need another tolerance, of 3000 on a circle 70.
+constexpr double kCutTol = 1e-12;
+constexpr int kCutTols = 7;
+template <class C>
+__device__ __forceinline__ int strict_site(C &c, const Site *__restrict__ sites, int64_t M, const BoxTree &tree,
+                                           const BoxArg &box, int64_t i, int32_t *nbr, int max_nbr, uint32_t &walls,
+                                           double &volume, double *bbox, int first)
+{
+    for (int t = first;; ++t) {
+        const bool last = t == kCutTols - 1;
+        const double tol = t == 1 ? 1e-11 : t == 2 ? 1e-10 : t == 3 ? 1e-9 : t == 4 ? 1e-13 : t == 5 ? 1e-14 : kCutTol;
+        const int n = wclip_site<C, true>(c, sites, M, tree, box, i, nbr, max_nbr, walls, volume, bbox, tol, last);
+        if (last || (n != -ERR_DEGENERATE && n != -ERR_OPEN)) return n;
+        lds_order();
+    }
 }
 
 }  // namespace vrt

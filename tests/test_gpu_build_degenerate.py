@@ -1,6 +1,7 @@
 """The builder on sites whose cells' faces nearly meet in one point: lattices
-disturbed along one axis by about the rounding of their coordinates, points on
-circles about one axis. Against the oracle's brute-force faces, with the
+disturbed by about the rounding of their coordinates, points on circles about
+one axis, points on spheres (whose bisectors all go through the centre, some
+within their rounding of one line). Against the oracle's brute-force faces, with the
 tolerances of the other tests of volumes and faces: 1e-9 of the volume, faces
 of more than 1e-9 of the cell's scale squared."""
 import numpy as np
@@ -55,4 +56,32 @@ def _circles(seed):
 @pytest.mark.parametrize("sites,seed", [(_near_lattice, 591), (_near_lattice, 1167), (_near_lattice, 1467),
                                         (_circles, 570), (_circles, 738), (_circles, 822)])
 def test_degenerate_in_the_loose_order(vrt, sites, seed):
+    _check(vrt, sites(seed))
+
+
+def _sphere(seed):
+    r = np.random.default_rng(seed)
+    d = r.normal(size=(1000 if seed % 2 else 100, 3))
+    return 0.7 * d / np.linalg.norm(d, axis=1, keepdims=True)
+
+
+def _spheres(seed):
+    r = np.random.default_rng(seed)
+    d = r.normal(size=(5, 200, 3))
+    d *= np.array([0.1, 0.2, 0.4, 0.6, 0.8])[:, None, None] / np.linalg.norm(d, axis=2, keepdims=True)
+    return d.reshape(-1, 3)
+
+
+def _rounded_lattice(seed):
+    r = np.random.default_rng(seed)
+    n = int(r.integers(5, 9))
+    m = (np.arange(n) + 0.5) / n * 2 - 1
+    s = np.stack(np.meshgrid(m, m, m, indexing="ij"), -1).reshape(-1, 3)
+    return s + r.normal(size=s.shape) * 10 ** r.uniform(-13, -11) * (r.random((len(s), 1)) < r.random())
+
+
+# Cells that a cut leaves as no closed polyhedron with the tolerance of all cells.
+@pytest.mark.parametrize("sites,seed", [(_sphere, 0), (_sphere, 1), (_sphere, 2), (_sphere, 3), (_spheres, 0), (_spheres, 1),
+                                        (_spheres, 2), (_spheres, 3)] + [(_rounded_lattice, k) for k in range(6)])
+def test_cells_are_closed(vrt, sites, seed):
     _check(vrt, sites(seed))
