@@ -441,22 +441,24 @@ __device__ __forceinline__ bool cuts_now(const C &c, const LaneVerts<C::kPerLane
 // Takes a batch of candidates, one per lane (site offset n, squared distance
 // d2, site j, act: there is one), nearest first. cull: test them all against
 // the cell beforehand; after a candidate that cut nothing the rest are
-// tested again. Returns 0 or an -ERR_* code.
+// tested again, if the cell has changed. Returns 0 or an -ERR_* code.
 constexpr int kCullMin = 6;   // fewer candidates are as well cut by one by one
 template <class C>
 __device__ __forceinline__ int wcell_take(C &c, LaneVerts<C::kPerLane> &R, double nx, double ny, double nz, double d2,
                                           int32_t j, bool act, bool cull)
 {
     const uint32_t key = high_word(d2);
+    bool tested = false;   // against the cell as it stands
     for (;;) {
         act = act && d2 < 4.0 * R.r2;
         uint64_t am = __ballot(act);
         if (am == 0) return 0;
-        if (cull && __popcll(am) >= kCullMin) {
+        if (cull && !tested && __popcll(am) >= kCullMin) {
             const bool cuts = cuts_now(c, R, nx, ny, nz, 0.5 * d2);
             act = act && cuts;
             am = __ballot(act);
             if (am == 0) return 0;
+            tested = true;
         }
         const uint32_t k = wave_min_u32(act ? key : 0xffffffffu);
         const int w = __ffsll((long long)__ballot(act && key == k)) - 1;
@@ -464,6 +466,7 @@ __device__ __forceinline__ int wcell_take(C &c, LaneVerts<C::kPerLane> &R, doubl
         const int rc = wcell_cut(c, R, lane_f64(nx, w), lane_f64(ny, w), lane_f64(nz, w), dd, (int32_t)lane_u32((uint32_t)j, w));
         if (rc < 0) return rc;
         act = act && lane_id() != w;
+        tested = tested && rc == 0;
         cull = rc == 0;
     }
 }
