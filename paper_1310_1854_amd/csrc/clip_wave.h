@@ -51,6 +51,8 @@
 // the lanes' FP64 registers they took 3.4 ms more.
 #pragma once
 
+#include <type_traits>
+
 #include "lanes.h"
 #include "vrt_internal.h"
 
@@ -91,8 +93,9 @@ struct WaveCell {
     int32_t id[P];          // internal site index, or -(w+1) for box wall w
     uint16_t rim[P];        // rim edges of the current cut
     static constexpr int kWait = kTable ? 64 : 1024;   // candidates that may wait between loads of 64
+    using Key = std::conditional_t<kTable, uint32_t, uint64_t>;
     int32_t buf[kWait + 64];                  // candidates waiting; the list of faces at the end
-    uint32_t key[kWait + 64];                 // high words of their squared distances
+    Key key[kWait + 64];                      // the bits of their squared distances (small cells: the high words)
     int32_t chunk[kTable ? 1 : 64];           // large cells: those taken together
     uint8_t twin[kTable ? P * P : 1];         // [a * P + b]: the vertex with the directed edge a -> b
     float4 ball[K * 64];    // every vertex in FP32 and scaled, with the squared radius of its (widened) ball;
@@ -150,7 +153,26 @@ __device__ __forceinline__ uint64_t wave_or_u64(uint64_t v)
     return v;
 }
 
+// Positive doubles compare as their bits do, and nearly so as their high words.
 __device__ __forceinline__ uint32_t high_word(double v) { return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32); }
+__device__ __forceinline__ uint32_t low_word(double v) { return (uint32_t)(uint64_t)__double_as_longlong(v); }
+template <class Key>
+__device__ __forceinline__ Key key_of(double v)
+{
+    return sizeof(Key) == 4 ? (Key)high_word(v) : (Key)(uint64_t)__double_as_longlong(v);
+}
+__device__ __forceinline__ uint32_t wave_min_key(uint32_t v) { return wave_min_u32(v); }
+__device__ __forceinline__ uint32_t wave_max_key(uint32_t v) { return wave_max_u32(v); }
+__device__ __forceinline__ uint64_t wave_min_key(uint64_t v)
+{
+    const uint32_t h = wave_min_u32((uint32_t)(v >> 32));
+    return (uint64_t)h << 32 | wave_min_u32((uint32_t)(v >> 32) == h ? (uint32_t)v : 0xffffffffu);
+}
+__device__ __forceinline__ uint64_t wave_max_key(uint64_t v)
+{
+    const uint32_t h = wave_max_u32((uint32_t)(v >> 32));
+    return (uint64_t)h << 32 | wave_max_u32((uint32_t)(v >> 32) == h ? (uint32_t)v : 0u);
+}
 
 // Vertex of planes a, b, p by Cramer's rule.
 __device__ __forceinline__ bool wvertex(const Plane &a, const Plane &b, const Plane &p, double &x, double &y, double &z)
@@ -439,11 +461,13 @@ __device__ __forceinline__ bool cuts_now(const C &c, const LaneVerts<C::kPerLane
 }
 
 // Takes a batch of candidates, one per lane (site offset n, squared distance
-// d2, site j, act: there is one), nearest first. cull: test them all against
-// the cell beforehand; after a candidate that cut nothing the rest are
+// d2, site j, act: there is one), nearest first (unless STRICT by the high
+// words alone; the strict order is exact, because the sites of a far cluster
+// share a high word and their planes are nearly parallel). cull: test them all
+// against the cell beforehand; after a candidate that cut nothing the rest are
 // tested again, if the cell has changed. Returns 0 or an -ERR_* code.
 constexpr int kCullMin = 6;   // fewer candidates are as well cut by one by one
-template <class C>
+template <bool STRICT, class C>
 __device__ __forceinline__ int wcell_take(C &c, LaneVerts<C::kPerLane> &R, double nx, double ny, double nz, double d2,
                                           int32_t j, bool act, bool cull)
 {
@@ -461,7 +485,12 @@ __device__ __forceinline__ int wcell_take(C &c, LaneVerts<C::kPerLane> &R, doubl
             tested = true;
         }
         const uint32_t k = wave_min_u32(act ? key : 0xffffffffu);
-        const int w = __ffsll((long long)__ballot(act && key == k)) - 1;
+        uint64_t first = __ballot(act && key == k);
+        if (STRICT && (first & (first - 1))) {
+            const uint32_t lo = wave_min_u32(act && key == k ? low_word(d2) : 0xffffffffu);
+            first = __ballot(act && key == k && low_word(d2) == lo);
+        }
+        const int w = __ffsll((long long)first) - 1;
         const double dd = 0.5 * lane_f64(d2, w);
         const int rc = wcell_cut(c, R, lane_f64(nx, w), lane_f64(ny, w), lane_f64(nz, w), dd, (int32_t)lane_u32((uint32_t)j, w));
         if (rc < 0) return rc;
@@ -599,17 +628,18 @@ __device__ __forceinline__ Box6 lane_box(const Box6 &b, int l)
     return o;
 }
 
-// The smallest double whose high word is above h.
-__device__ __forceinline__ double above(uint32_t h) { return __longlong_as_double((long long)((uint64_t)(h + 1u) << 32)); }
+// The smallest double whose key is above k.
+__device__ __forceinline__ double above(uint32_t k) { return __longlong_as_double((long long)((uint64_t)(k + 1u) << 32)); }
+__device__ __forceinline__ double above(uint64_t k) { return __longlong_as_double((long long)(k + 1u)); }
 
 // How many of the n waiting candidates have a key in [k0, k1].
 template <class C>
-__device__ __forceinline__ int count_waiting(const C &c, int n, uint32_t k0, uint32_t k1)
+__device__ __forceinline__ int count_waiting(const C &c, int n, typename C::Key k0, typename C::Key k1)
 {
     int m = 0;
     for (int e = 0; e < n; e += 64) {
         const int at = e + lane_id();
-        const uint32_t k = c.key[at < n ? at : 0];
+        const typename C::Key k = c.key[at < n ? at : 0];
         m += __popcll(__ballot(at < n && k >= k0 && k <= k1));
     }
     return m;
@@ -620,24 +650,25 @@ __device__ __forceinline__ int count_waiting(const C &c, int n, uint32_t k0, uin
 // it, at least three quarters of that), their number in m. With more than
 // `most` at the smallest key, that key and their number.
 template <class C>
-__device__ __forceinline__ uint32_t nearest_waiting(const C &c, int n, uint32_t k0, int most, int &m)
+__device__ __forceinline__ typename C::Key nearest_waiting(const C &c, int n, typename C::Key k0, int most, int &m)
 {
-    uint32_t lo = 0xffffffffu, hi = 0;
+    using Key = typename C::Key;
+    Key lo = ~(Key)0, hi = 0;
     for (int e = 0; e < n; e += 64) {
         const int at = e + lane_id();
-        const uint32_t k = c.key[at < n ? at : 0];
+        const Key k = c.key[at < n ? at : 0];
         if (at < n && k >= k0) {
             lo = min(lo, k);
             hi = max(hi, k);
         }
     }
-    lo = wave_min_u32(lo);
-    hi = wave_max_u32(hi);
+    lo = wave_min_key(lo);
+    hi = wave_max_key(hi);
     m = count_waiting(c, n, k0, hi);
     if (m <= most) return hi;
     m = count_waiting(c, n, k0, lo);
     while (hi - lo > 1 && 4 * m < 3 * most) {   // count(lo) <= most < count(hi)
-        const uint32_t mid = lo + (hi - lo) / 2;
+        const Key mid = lo + (hi - lo) / 2;
         const int k = count_waiting(c, n, k0, mid);
         if (k > most) {
             hi = mid;
@@ -651,13 +682,13 @@ __device__ __forceinline__ uint32_t nearest_waiting(const C &c, int n, uint32_t 
 
 // Drops the waiting candidates with keys above k1. Returns how many stay.
 template <class C>
-__device__ __forceinline__ int drop_waiting(C &c, int n, uint32_t k1)
+__device__ __forceinline__ int drop_waiting(C &c, int n, typename C::Key k1)
 {
     const uint64_t lt = lanemask_lt();
     int kept = 0;
     for (int e = 0; e < n; e += 64) {   // in place: nothing moves up
         const int at = e + lane_id();
-        const uint32_t k = at < n ? c.key[at] : 0xffffffffu;
+        const typename C::Key k = at < n ? c.key[at] : 0;
         const int32_t j = at < n ? c.buf[at] : 0;
         const bool stay = at < n && k <= k1;
         const uint64_t bal = __ballot(stay);
@@ -827,14 +858,14 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
             else k0 = mid + 1;
         }
         if (!STRICT || M <= 64) {
-            const int rc = wcell_take(c, R, dx, dy, dz, d2, (int32_t)j, act && key <= near, false);
+            const int rc = wcell_take<STRICT>(c, R, dx, dy, dz, d2, (int32_t)j, act && key <= near, false);
             if (rc < 0) return rc;
         }
     }
     // Everything else in reach, through the tree of boxes, in shells of
     // squared distance [from, to), cut back whenever more than C::kWait sites
     // wait, so that the sites are taken nearest first (a cell still open on one
-    // side would otherwise grow hundreds of faces against far sites). Distances are told apart by their high words.
+    // side would otherwise grow hundreds of faces against far sites).
     double from = 0.0, to = 4.0 * above(near);
     while (M > 64) {
         int nbuf = 0;
@@ -856,7 +887,7 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
             const Site o = sites[j];
             const double dx = o.x - p[0], dy = o.y - p[1], dz = o.z - p[2];
             const double d2 = dx * dx + dy * dy + dz * dz;
-            return wcell_take(c, R, dx, dy, dz, d2, j, act, true);
+            return wcell_take<STRICT>(c, R, dx, dy, dz, d2, j, act, true);
         };
         auto take_waiting = [&]() {   // all of them, nearest first
             int rc = 0;
@@ -864,15 +895,15 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
                 rc = take(c.buf, min(nbuf, 64));
                 if (rc >= 0 && nbuf > 64) rc = take(c.buf + 64, nbuf - 64);
             } else {
-                uint32_t k0 = 0;
+                typename C::Key k0 = 0;
                 for (int left = nbuf; left > 0 && rc >= 0;) {
                     int m;
-                    const uint32_t k1 = nearest_waiting(c, nbuf, k0, 64, m);
+                    const typename C::Key k1 = nearest_waiting(c, nbuf, k0, 64, m);
                     for (int first = 0; first < m && rc >= 0; first += 64) {   // several rounds of equal keys only
                         int at = 0;
                         lds_order();
                         for (int e = 0; e < nbuf; e += 64) {
-                            const uint32_t k = c.key[e + l < nbuf ? e + l : 0];
+                            const typename C::Key k = c.key[e + l < nbuf ? e + l : 0];
                             const bool in = e + l < nbuf && k >= k0 && k <= k1;
                             const uint64_t bal = __ballot(in);
                             const int to_ = at + __popcll(bal & lt) - first;
@@ -932,17 +963,19 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
                         if (want) {
                             const int at = nbuf + __popcll(wm & lt);
                             c.buf[at] = (int32_t)j;
-                            c.key[at] = key;
+                            c.key[at] = key_of<typename C::Key>(d2);
                         }
                         nbuf += __popcll(wm);
                         lds_order();
                         if (nbuf > C::kWait) {
                             int m;
-                            const uint32_t k1 = nearest_waiting(c, nbuf, 0u, C::kWait, m);
+                            const typename C::Key k1 = nearest_waiting(c, nbuf, (typename C::Key)0, C::kWait, m);
                             if (m <= C::kWait) {
                                 nbuf = drop_waiting(c, nbuf, k1);
                                 to = above(k1);
                                 crowded = true;
+                            } else if (STRICT && C::kTable) {   // too many with one high word: their order is lost
+                                return -ERR_CAPACITY;
                             } else {   // too many at one distance: take all that wait now
                                 const int rc = take_waiting();
                                 if (rc < 0) return rc;

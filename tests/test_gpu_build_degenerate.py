@@ -1,7 +1,7 @@
 """The builder on sites whose cells' faces nearly meet in one point: lattices
 disturbed by about the rounding of their coordinates, points on circles about
 one axis, points on spheres (whose bisectors all go through the centre, some
-within their rounding of one line). Against the oracle's brute-force faces, with the
+within their rounding of one line), far clusters. Against the oracle's brute-force faces, with the
 tolerances of the other tests of volumes and faces: 1e-9 of the volume, faces
 of more than 1e-9 of the cell's scale squared."""
 import numpy as np
@@ -84,4 +84,27 @@ def _rounded_lattice(seed):
 @pytest.mark.parametrize("sites,seed", [(_sphere, 0), (_sphere, 1), (_sphere, 2), (_sphere, 3), (_spheres, 0), (_spheres, 1),
                                         (_spheres, 2), (_spheres, 3)] + [(_rounded_lattice, k) for k in range(6)])
 def test_cells_are_closed(vrt, sites, seed):
+    _check(vrt, sites(seed))
+
+
+def _far_cluster(seed):
+    r = np.random.default_rng(seed)
+    n = int(np.exp(r.uniform(np.log(70), np.log(900)))) // 2
+    size = 10 ** r.uniform(-6, -2)
+    d = r.normal(size=(n, 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    return np.concatenate([size * d + r.uniform(-0.5, 0.5, 3), r.uniform(-1, 1, (n, 3))])
+
+
+def _rounded_points(seed):
+    r = np.random.default_rng(seed)
+    n = int(np.exp(r.uniform(np.log(70), np.log(900))))
+    s = np.unique(r.integers(-6, 7, (n, 3)) / 6.5, axis=0)
+    return s + r.normal(size=s.shape) * 10 ** r.uniform(-16, -11)
+
+
+# Cells that need their planes in the exact order of distance: planes of a far cluster's sites, nearly parallel, at
+# distances equal to 2^-20; lattice points with distances equal to the disturbance of their coordinates.
+@pytest.mark.parametrize("sites,seed", [(_far_cluster, 2349), (_rounded_points, 2012), (_rounded_points, 4604)])
+def test_planes_come_in_the_exact_order(vrt, sites, seed):
     _check(vrt, sites(seed))
