@@ -214,10 +214,11 @@ inline WalkView walk_view(const Grid &g)
 // than the table's own tolerance then lies in the cell, so no other site's
 // bisector comes nearer, and none of them is so close to the cell's site
 // that the computed distances could not tell them apart: the neighbours'
-// bisectors leave a ball of 5e-6 d_m around it.) Returns -1 when the margin
-// is not there (on or next to a boundary, as lattice points are): the caller
-// then searches. The user index goes to *uid.
-__device__ __forceinline__ int32_t walk_to_site(const WalkView &V, const double q[3], int32_t *uid)
+// bisectors leave a ball of 5e-6 d_m around it.) So is a site that q coincides
+// with. Returns -1 when the margin is not there (on or next to a boundary, as
+// lattice points are): the caller then searches the ball around q that the last
+// site lies on, r2 being its squared distance. The user index goes to *uid.
+__device__ __forceinline__ int32_t walk_to_site(const WalkView &V, const double q[3], int32_t *uid, double &r2)
 {
     const uint32_t key = hilbert_key(key_coord(q[0], V.lo[0], V.scale), key_coord(q[1], V.lo[1], V.scale),
                                      key_coord(q[2], V.lo[2], V.scale));
@@ -232,6 +233,11 @@ __device__ __forceinline__ int32_t walk_to_site(const WalkView &V, const double 
         const int n = s2.z;
         const double ex = q[0] - s0.x, ey = q[1] - s0.y, ez = q[2] - s1.x;
         const double d2m = ex * ex + ey * ey + ez * ez;
+        r2 = d2m;
+        if (d2m == 0.0) {
+            *uid = s2.x;
+            return s2.y;
+        }
         const double c = 2e-9 * sqrt(d2m) + V.sure, c2 = c * c;
         double best = d2m;
         int w = -1;

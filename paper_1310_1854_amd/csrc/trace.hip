@@ -504,12 +504,17 @@ __global__ void k_fill_i64(int64_t *p, int64_t n, int64_t v)
         p[i] = v;
 }
 
-// The cell of each point: by a walk along the neighbour table (W.seed set),
-// and by the ring search of the bucket grid where that is not sure of its
-// answer. A point's walk reads two or three cells' blocks, whatever the
-// density, where rings of uniform buckets are crowded here and empty there:
-// 5x10^6 points uniform over a 10^6-site flared disc take 1.2 ms (by rings
-// alone 11.7 ms).
+// The cell of each point: by a walk along the neighbour table (W.seed set)
+// and, where that is not sure of its answer, by a search of the buckets that
+// the ball through the site it ended at meets; else by the ring search. A
+// point's walk reads two or three cells' blocks, whatever the density, where
+// rings of uniform buckets are crowded here and empty there. 10^6
+// points (us), by rings alone / by the walk:
+//   10^6-site flared disc   uniform 3870/286    on a wall 12800/4020   multiples of 1/64 of the box 4180/542
+//   10^5-site cube          uniform 373/205     on a wall   956/566    at sites 42/69
+//   cubic lattice, 64^3     uniform 482/86      midpoints   500/205    at sites 47/51
+// Few sites have few buckets to look into: 16 of them 66/82, 32 of them 132/80.
+constexpr int64_t kWalkMinSites = 32;
 __global__ void __launch_bounds__(256) k_locate(BucketGridView g, WalkView W, const double *__restrict__ pts, int64_t N,
                                                 int32_t *__restrict__ cell)
 {
@@ -522,7 +527,9 @@ __global__ void __launch_bounds__(256) k_locate(BucketGridView g, WalkView W, co
         return;
     }
     int32_t uid;
-    if (!W.seed || walk_to_site(W, q, &uid) < 0) nearest_site(g, q, &uid);
+    double r2;
+    if (!W.seed) nearest_site(g, q, &uid);
+    else if (walk_to_site(W, q, &uid, r2) < 0) nearest_within(g, q, r2, &uid);
     cell[i] = uid;
 }
 
@@ -568,7 +575,7 @@ extern "C" vor_status vor_locate(const vor_grid *G, const double *pts, int64_t N
     int64_t blocks = (N + T - 1) / T;
     if (blocks > 0x7fffffff) return VOR_EINVAL;
     WalkView W = walk_view(g);
-    if (g.rows_cut) W.seed = nullptr;
+    if (g.rows_cut || g.M < kWalkMinSites) W.seed = nullptr;
     hipLaunchKernelGGL(k_locate, dim3((unsigned)blocks), dim3(T), 0, (hipStream_t)stream, bucket_view(g), W, pts, N, cell);
     return hipGetLastError() == hipSuccess ? VOR_OK : VOR_EDEVICE;
 }

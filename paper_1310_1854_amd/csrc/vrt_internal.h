@@ -266,6 +266,42 @@ VRT_HD inline int32_t nearest_site(const BucketGridView &g, const double q[3], i
     return best_i;
 }
 
+// The nearest site (internal index; equal distances: the lower user index) of
+// a point inside the box whose nearest is known to lie within r2 (squared
+// distance, infinite: not known): every site in the buckets that the ball
+// meets, whose rows of buckets along x are contiguous. The distances are those
+// of nearest_site, and so is the result.
+VRT_HD inline int32_t nearest_within(const BucketGridView &g, const double q[3], double r2, int32_t *uid_out)
+{
+    const double r = sqrt(r2) * (1.0 + 1e-12);
+    int b0[3], b1[3];
+    for (int a = 0; a < 3; ++a) {   // (the ends stay in the box: a bucket coordinate is an int)
+        const double lo = q[a] - r, hi = q[a] + r;
+        b0[a] = lo > g.lo[a] ? bucket_coord(lo, g.lo[a], g.inv_h[a], g.dims[a]) : 0;
+        b1[a] = hi < g.hi[a] ? bucket_coord(hi, g.lo[a], g.inv_h[a], g.dims[a]) : g.dims[a] - 1;
+    }
+    double best = 1e308 * 10.0;
+    int32_t best_i = -1, best_u = 0x7fffffff;
+    for (int z = b0[2]; z <= b1[2]; ++z)
+        for (int y = b0[1]; y <= b1[1]; ++y) {
+            const int row = (z * g.dims[1] + y) * g.dims[0];
+            const int s1 = g.start[row + b1[0] + 1];
+            for (int s = g.start[row + b0[0]]; s < s1; ++s) {
+                const Site p = g.items[s];
+                const double dx = q[0] - p.x, dy = q[1] - p.y, dz = q[2] - p.z;
+                const double d = dx * dx + dy * dy + dz * dz;
+                const int32_t uid = (int32_t)(p.uid >> 32);
+                if (d < best || (d == best && uid < best_u)) {
+                    best = d;
+                    best_i = (int32_t)(p.uid & 0xffffffff);
+                    best_u = uid;
+                }
+            }
+        }
+    *uid_out = best_u;
+    return best_i;
+}
+
 constexpr int kHilbertBits10 = 10;   // bits per axis of the Hilbert keys
 
 // Hilbert index of a point with kHilbertBits10-bit integer coordinates, by
