@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(256) k_serve_group(const GridRef *__restrict__
             if (loc.start) m = nearest_in_blocks_wave<W>(loc, p);
             if (m < 0) m = nearest_site_wave<W>(G.grid, p, nullptr);
             R.s_c = s0;
-            group_walk<MODE, true, false, true, W>(G, I, O, Extras{}, R, S, m);
+            group_walk<MODE, true, false, true, W>(G, I, O, Extras{}, R, S, m, nullptr);
         }
         if (li == 0) {
             if (R.cap > 0 && R.st == RAY_OK && S.cnt > R.cap && R.chunk == -2) {   // its spill chunks ran out

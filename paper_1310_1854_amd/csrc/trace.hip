@@ -324,8 +324,10 @@ __global__ void __launch_bounds__(256) k_trace_group(TraceArgs A)
     constexpr int W = kGroupLanes;
     __shared__ unsigned long long sum[7];
     __shared__ int ended;
+    __shared__ GroupTally tally;   // (EXT)
     if (threadIdx.x < 7) sum[threadIdx.x] = 0;
     if (threadIdx.x == 7) ended = 0;
+    if (EXT) tally_clear(tally);
     __syncthreads();
     const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) / W;
     const int li = threadIdx.x & (W - 1);
@@ -350,7 +352,7 @@ __global__ void __launch_bounds__(256) k_trace_group(TraceArgs A)
                 if (A.start && li == 0) A.start[ray] = m;
             }
             R.s_c = s0;
-            group_walk<MODE, SEGS, EXT, false, W>(A.G, A.I, A.O, A.X, R, S, m);
+            group_walk<MODE, SEGS, EXT, false, W>(A.G, A.I, A.O, A.X, R, S, m, EXT && A.N >= GroupTally::kMinRays ? &tally : nullptr);
         } else {
             R.L = 0.0;
             if (EXT) ray_extras_begin(A.X, ray, R);
@@ -365,7 +367,8 @@ __global__ void __launch_bounds__(256) k_trace_group(TraceArgs A)
             atomicAdd(&sum[4], (unsigned long long)S.recs);
         }
     }
-    if (!A.counters) return;
+    const bool tallies = EXT && (A.X.tally_len || A.X.tally_abs);
+    if (!A.counters && !tallies) return;
     if (A.persistent) {   // a wave runs as long as its longest path
         int it = S.steps;
         for (int off = 32; off > 0; off >>= 1) it = max(it, __shfl_xor(it, off, 64));
@@ -377,8 +380,9 @@ __global__ void __launch_bounds__(256) k_trace_group(TraceArgs A)
     int at = 0;
     if ((threadIdx.x & 63) == 0) at = __hip_atomic_fetch_add(&ended, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (__shfl(at, 0, 64) == 3) {   // the block's last wave
+        if (tallies) tally_flush(A.X, tally);
         const int i = threadIdx.x & 63;
-        const unsigned long long v = i < 7 ? __hip_atomic_load(&sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0ull;
+        const unsigned long long v = A.counters && i < 7 ? __hip_atomic_load(&sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0ull;
         if (v) atomicAdd(&A.counters[i], v);
     }
 }
@@ -590,27 +594,24 @@ int resident_blocks_per_cu(K kernel)
     return n;
 }
 
-// Up to how many rays a launch gives each ray a group of lanes: about where
-// one ray per lane becomes the faster one on some grid. Kernel times of one
-// ray per lane / per group (us):
-//   rays                       61      1000     20000      40000      80000     160000
-//   mixed, windows
-//     exp. disc, 10^5     478/153   956/277  1019/452   1045/732  1077/1239  1146/1417
-//     flared disc, 10^6  1109/306  1452/417  1812/802  2026/1203  1991/1823  2296/2834
-//     clumpy, 3x10^6     1418/358  1854/518 2124/1161  2052/1928  2309/3354  2689/3691
-//   FP64, windows
-//     exp. disc           612/135  1322/248  1332/398   1437/660  1626/1095  1647/1271
-//     flared disc        1293/268  1998/366  2668/719  2803/1099  3183/1677  3634/2558
-//     clumpy             1816/310  2250/450  2676/933  2629/1586  3302/2826  4819/3220
-// FP64 without segments, at 260000 and 400000: 1874/1322 and 2309/1875 on the
-// exponential disc, 6399/3824 and 7521/5721 on the clumpy medium. With the
-// transport outputs the tally atomics cost the groups more (they deposit
-// one by one): clumpy, 40000 and 80000 rays in FP64 2932/2499 and 3916/4347.
+// Up to how many rays per compute unit a launch gives each ray a group of
+// lanes: where one ray per lane becomes the faster one for some rays. Rays from
+// one point are the first, as the lanes of a wave then meet the same cells.
+// Time of one ray per lane over that per group, the least and the median of ten
+// sets of rays (from one point and from all over: cubes of 10^3 and 10^5 sites,
+// two discs, a clumpy medium) on 256 units, whole calls:
+//   rays           32768      40960      65536      81920     98304     131072    262144
+//   FP64 windows   1.22 1.75  1.15 1.48  0.89 1.16            0.74 1.14           (57000: 1.10 1.45)
+//   FP64 depths    1.28 2.23  1.30 1.91  1.05 1.42  1.04 1.35 0.90 1.28 0.79 1.23 0.71 1.22
+//   mixed windows  1.06 1.18  0.91 1.19
+//   mixed depths   1.17 1.43  1.00 1.23  0.80 1.18
+// With tallies (20 sets; GroupTally): FP64 20000 1.18 1.86, 32768 1.06 1.39,
+// 40960 0.94 1.16; mixed 20000 1.08 1.30, 32768 0.88 1.05.
 template <int MODE, bool SEGS, bool EXT>
-constexpr int64_t group_max_rays()
+constexpr int64_t group_max_rays_per_cu()
 {
-    if (MODE == VOR_MODE_FP64) return EXT ? 40960 : SEGS ? 98304 : 262144;
-    return EXT ? 32768 : SEGS ? 40960 : 65536;
+    if (MODE == VOR_MODE_FP64) return EXT ? 160 : SEGS ? 224 : 320;
+    return EXT ? 80 : SEGS ? 128 : 160;
 }
 
 // Launch of the trace kernel: one ray per group of lanes, or the start cells
@@ -621,7 +622,7 @@ template <int MODE, bool SEGS, bool EXT>
 vor_status launch_trace_ext(const TraceArgs &A, bool persistent, int cus, hipStream_t st)
 {
     constexpr int T = 256;
-    if (A.N <= group_max_rays<MODE, SEGS, EXT>()) {
+    if (A.N <= cus * group_max_rays_per_cu<MODE, SEGS, EXT>()) {
         constexpr int rays = T / kGroupLanes;
         hipLaunchKernelGGL((k_trace_group<MODE, SEGS, EXT>), dim3((unsigned)((A.N + rays - 1) / rays)), dim3(T), 0, st, A);
         return VOR_OK;
