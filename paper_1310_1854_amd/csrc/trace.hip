@@ -36,6 +36,8 @@ struct TraceArgs {
     Extras X;             // interaction points and tallies (kernels with EXT only)
     int32_t start_given;  // start holds the cells already
     int32_t persistent;   // the caller asked for persistent waves, and with them for their counters
+    int32_t few_blocks;   // persistent kernel: the blocks past these end at once unless the rays are coherent, as
+    int32_t samples;      // work[kCoherent] of the start pass's waves say that it looked at (0: it did not)
 };
 
 #ifndef VRT_REFILL_MIN
@@ -62,6 +64,11 @@ constexpr int kRefillMin = VRT_REFILL_MIN;   // idle lanes that trigger a refill
 constexpr int kParts = 8;
 constexpr int kHead0 = 8;
 static_assert(kHead0 + kParts <= VOR_WORK_WORDS, "work queue heads must fit the control words");
+// The start pass looks at the waves of every kSampleBlocks-th block (atomics on
+// one word take turns) and counts in work[kCoherent] those whose rays all start
+// at one point.
+constexpr int kCoherent = 3;
+constexpr int kSampleBlocks = 32;
 
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v)
 {
@@ -160,6 +167,11 @@ __global__ void __launch_bounds__(256) k_start_cells(TraceArgs A)
     const uint8_t st = valid ? ray_setup(A.G, A.I, ray, r0, k, L, s0) : (uint8_t)RAY_BADDIR;
     double q[3];
     start_point(r0, k, s0, q);
+    if (A.samples && blockIdx.x % kSampleBlocks == 0) {
+        const double q0 = __shfl(q[0], 0, 64), q1 = __shfl(q[1], 0, 64), q2 = __shfl(q[2], 0, 64);
+        const bool same = valid && st == RAY_OK && q[0] == q0 && q[1] == q1 && q[2] == q2;
+        if (__ballot(same) == ~0ull && (threadIdx.x & 63) == 0) atomicAdd((unsigned long long *)&A.work[kCoherent], 1ull);
+    }
     const int32_t m = start_cell(A.G.grid, A.loc, q, valid && st == RAY_OK);
     if (valid) A.start[ray] = m;
 }
@@ -231,6 +243,7 @@ __device__ __forceinline__ void flush_deposits(const Extras &X, RayState &R)
 template <int MODE, bool SEGS, bool EXT>
 __global__ void __launch_bounds__(256) VRT_OCC k_trace_persistent(TraceArgs A)
 {
+    if ((int)blockIdx.x >= A.few_blocks && 4 * A.work[kCoherent] < 3 * (int64_t)A.samples) return;
     const int lane = threadIdx.x & 63;
     const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
     RayStats S, T;   // S: current ray, T: totals of this lane
@@ -619,7 +632,7 @@ constexpr int64_t group_max_rays_per_cu()
 // device at once; cus = the grid's device's compute units, read when the
 // grid was built).
 template <int MODE, bool SEGS, bool EXT>
-vor_status launch_trace_ext(const TraceArgs &A, bool persistent, int cus, hipStream_t st)
+vor_status launch_trace_ext(TraceArgs A, bool persistent, int cus, hipStream_t st)
 {
     constexpr int T = 256;
     if (A.N <= cus * group_max_rays_per_cu<MODE, SEGS, EXT>()) {
@@ -627,11 +640,13 @@ vor_status launch_trace_ext(const TraceArgs &A, bool persistent, int cus, hipStr
         hipLaunchKernelGGL((k_trace_group<MODE, SEGS, EXT>), dim3((unsigned)((A.N + rays - 1) / rays)), dim3(T), 0, st, A);
         return VOR_OK;
     }
-    if (A.start && !A.start_given)
-        hipLaunchKernelGGL(k_start_cells, dim3((unsigned)((A.N + T - 1) / T)), dim3(T), 0, st, A);
+    const int64_t rounds = (A.N + T - 1) / T;   // blocks of the start pass
+    const bool starts = A.start && !A.start_given;
+    if (persistent && starts) A.samples = (int32_t)((rounds + kSampleBlocks - 1) / kSampleBlocks * (T / 64));
+    if (starts) hipLaunchKernelGGL(k_start_cells, dim3((unsigned)rounds), dim3(T), 0, st, A);
     if (persistent) {
         static const int per_cu = resident_blocks_per_cu(k_trace_persistent<MODE, SEGS, EXT>);
-        // How many of the blocks that fit are launched: with few rays per lane
+        // How many of the blocks that fit take part: with few rays per lane
         // more waves only mean shorter queues and more idle lanes at the end,
         // and FP64's fourth block per unit costs more in L2 misses than it
         // hides. Whole calls (us) with 2 / 3 / 4 blocks per unit:
@@ -644,9 +659,17 @@ vor_status launch_trace_ext(const TraceArgs &A, bool persistent, int cus, hipStr
         // and without segments, where the fourth block pays on long queues:
         //   flared disc  10^6           7182/6647/7247          4352/3785/3965
         //               4x10^6         24730/21408/21330       14877/12374/12136
+        // (FP64 over a table past the last-level cache is fastest with two, as
+        // the clumpy medium shows; the rule does not look at the table.) Rays
+        // from one point share their cells, so that all the blocks that fit
+        // pay: 400000 of them without segments in a clumpy medium 3130 us with
+        // all, 3760 with two per unit. The start pass sees it, and the kernel's
+        // further blocks end at once where it is not so; without that pass the
+        // rule is as for any rays.
         const int64_t turn = (int64_t)cus * T;
         const int most = A.N < 8 * turn ? 2 : SEGS || A.N < 48 * turn ? 3 : 4;
-        const int64_t blocks = std::min<int64_t>((int64_t)cus * std::min(per_cu, most), (A.N + T - 1) / T);
+        A.few_blocks = cus * std::min(per_cu, most);
+        const int64_t blocks = std::min<int64_t>(A.samples ? (int64_t)cus * per_cu : A.few_blocks, rounds);
         hipLaunchKernelGGL((k_trace_persistent<MODE, SEGS, EXT>), dim3((unsigned)std::max<int64_t>(blocks, 1)),
                            dim3(T), 0, st, A);
     } else {
@@ -733,6 +756,7 @@ extern "C" vor_status vor_trace(const vor_grid *G, const double *origins, const 
     if (A.work) hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(64), 0, st, A.work, VOR_WORK_WORDS);
     A.start_given = opts && opts->start_given;
     A.persistent = persistent;
+    A.few_blocks = A.samples = 0;
     if (spill) {
         int64_t nb = std::min<int64_t>((N + T - 1) / T, 65535);
         hipLaunchKernelGGL(k_fill_i64, dim3((unsigned)nb), dim3(T), 0, st, A.O.spill_first, N, (int64_t)-1);
