@@ -403,11 +403,26 @@ __global__ void __launch_bounds__(256) k_serve_group(const GridRef *__restrict__
     }
 }
 
-// Up to how many rays of a class (FP64, mixed, mixed over compact records) a
-// launch gives each ray a group of lanes. 12 requests of 256 to 65536 rays
-// over three grids, whole client loop: 6.23 ms with one ray per lane, 4.43 ms
-// with these; 12 of 64 to 1000 rays: 5.10 and 1.86 ms.
-constexpr int64_t kGroupServeRays[3] = {131072, 65536, 65536};
+// Up to how many rays of a class (FP64, mixed, mixed over compact records) per
+// compute unit and grid a launch gives each ray a group of lanes, a ray counted
+// as the part of a path through the class's largest grid that its own is (by
+// the cube root of the sites). The time of the groups is that of all steps;
+// one ray per lane takes as long as the longest path, but for each grid anew,
+// as a wave holds the rays of one. Time of one ray per lane over that per
+// group, the least and the median, requests to 256 units (rays from one point,
+// the least, and from all over; cubes, two discs, a clumpy medium; up to four
+// requests a grid):
+//   rays             24000      32768      48000      65536-72000  96000      131072
+//   FP64  one grid              0.89 1.51  0.67 1.13  0.53 0.95    0.50 0.80  0.37 0.61
+//         two grids  2.46 2.88             1.32 1.82  1.15 1.38    0.83 1.16  0.66 0.88
+//         three      2.70 3.06             1.81 2.19  1.27 1.62    0.99 1.32  0.91 1.13
+//         four       2.72 3.35             2.01 2.26  1.43 1.73    1.22 1.47  0.97 1.21
+//   mixed one grid   (16384: 1.00 1.63)    0.50 0.99  0.39 0.71
+//         two grids  1.76 2.02             1.00 1.24  0.79 0.97    0.55 0.88  0.42 0.90
+//         three      1.77 2.10             1.19 1.50  0.84 1.11    0.64 0.82  0.69 0.96
+//         four       1.99 2.18             1.43 1.58  0.98 1.13    0.76 0.98  0.69 0.92
+constexpr int kGroupServeRays[3] = {112, 56, 56};
+constexpr int kGroupServeGrids = 3;   // more than these count as so many
 
 __global__ void k_zero_launch(unsigned int *head, unsigned long long *counters, ReqCount *rc, int n_req)
 {
@@ -659,10 +674,23 @@ struct vor_server {
             return (ka != kb) ? ka < kb : reqs[x].grid < reqs[y].grid;
         });
         int64_t cls_rays[3] = {0, 0, 0};
-        for (int64_t id : L.reqs) cls_rays[kernel_class(reqs[id])] += reqs[id].n;
+        double cls_steps[3] = {0.0, 0.0, 0.0}, longest[3] = {0.0, 0.0, 0.0};
+        int cls_grids[3] = {0, 0, 0}, last[3] = {-1, -1, -1};
+        for (int64_t id : L.reqs) {   // (in order of class and grid)
+            const Request &r = reqs[id];
+            const int c = kernel_class(r);
+            const double steps = std::cbrt((double)vrt_grid_of(grids[r.grid]).M);
+            cls_rays[c] += r.n;
+            cls_steps[c] += steps * (double)r.n;
+            longest[c] = std::max(longest[c], steps);
+            cls_grids[c] += r.grid != last[c];
+            last[c] = r.grid;
+        }
+        const int cus = vrt_grid_of(grids[0]).cus;
         bool group[3];   // classes with few rays in the launch: a group of lanes per ray, in small chunks
         for (int c = 0; c < 3; ++c) {
-            group[c] = cls_rays[c] <= kGroupServeRays[c] &&
+            const double most = (double)cus * kGroupServeRays[c] * std::min(cls_grids[c], kGroupServeGrids);
+            group[c] = cls_steps[c] <= most * longest[c] &&
                        nch_total + cls_rays[c] / kGroupChunk + (int64_t)L.reqs.size() <= kMaxLaunchChunks;
             if (group[c]) nch_total += cls_rays[c] / kGroupChunk + (int64_t)L.reqs.size();   // chunks more, at most
         }
