@@ -12,6 +12,7 @@
 //  5. make the lists symmetric, order each row nearest neighbour first, and
 //     lay out the trace records (FP64 sites and FP32 offsets per neighbour,
 //     CSR by cell).
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -1051,41 +1052,44 @@ extern "C" vor_status vor_grid_truncate_row(vor_grid *G, int64_t site, int32_t k
     if (hipMemcpy(&i, g.inv_perm + site, sizeof(i), hipMemcpyDeviceToHost) != hipSuccess ||
         hipMemcpy(&rw, g.rows + i, sizeof(rw), hipMemcpyDeviceToHost) != hipSuccess)
         return VOR_EDEVICE;
-    if (keep < rw.y) {
-        g.rows_cut = 1;   // no more walks along the table
-        // the block offsets follow the records (12 or 8 bytes each): move the
-        // first keep of them to their place after the first keep records
-        int32_t bo = block_of(rw, i);
-        if (g.blk_off && hipMemcpy(&bo, g.blk_off + i, sizeof(bo), hipMemcpyDeviceToHost) != hipSuccess)
-            return VOR_EDEVICE;
-        char *rec = reinterpret_cast<char *>(g.blk + bo + kHdrSlots);
-        const int rbytes = g.compact ? 8 : 12;
-        std::vector<int32_t> nb(keep > 0 ? keep : 1);
-        if (keep > 0 && (hipMemcpy(nb.data(), rec + rbytes * rw.y, sizeof(int32_t) * keep, hipMemcpyDeviceToHost) !=
-                             hipSuccess ||
-                         hipMemcpy(rec + rbytes * keep, nb.data(), sizeof(int32_t) * keep, hipMemcpyHostToDevice) !=
-                             hipSuccess))
-            return VOR_EDEVICE;
-        BlockHdr *h = reinterpret_cast<BlockHdr *>(g.blk + bo);
-        int32_t len = 0;
-        if (hipMemcpy(&len, &h->len, sizeof(len), hipMemcpyDeviceToHost) != hipSuccess) return VOR_EDEVICE;
-        len = (len & ~kLenMask) | keep;   // the scale exponent stays
-        // the same in the FP64 block (24-byte records)
-        int32_t bo64 = 0;
-        if (hipMemcpy(&bo64, g.blk64_off + i, sizeof(bo64), hipMemcpyDeviceToHost) != hipSuccess) return VOR_EDEVICE;
-        char *rec64 = reinterpret_cast<char *>(g.blk64 + bo64 + kHdrSlots);
-        if (keep > 0 && (hipMemcpy(nb.data(), rec64 + 24 * rw.y, sizeof(int32_t) * keep, hipMemcpyDeviceToHost) !=
-                             hipSuccess ||
-                         hipMemcpy(rec64 + 24 * keep, nb.data(), sizeof(int32_t) * keep, hipMemcpyHostToDevice) !=
-                             hipSuccess))
-            return VOR_EDEVICE;
-        BlockHdr *h64 = reinterpret_cast<BlockHdr *>(g.blk64 + bo64);
-        rw.y = keep;
-        if (hipMemcpy(g.rows + i, &rw, sizeof(rw), hipMemcpyHostToDevice) != hipSuccess ||
-            hipMemcpy(&h->len, &len, sizeof(len), hipMemcpyHostToDevice) != hipSuccess ||
-            hipMemcpy(&h64->len, &keep, sizeof(keep), hipMemcpyHostToDevice) != hipSuccess)
-            return VOR_EDEVICE;
-    }
+    if (keep >= rw.y) return VOR_OK;
+    g.rows_cut = 1;   // no more walks along the table
+    const int n = rw.y;
+    std::vector<Rec64> rec(n);
+    if (hipMemcpy(rec.data(), g.rec64 + rw.x, sizeof(Rec64) * n, hipMemcpyDeviceToHost) != hipSuccess) return VOR_EDEVICE;
+    // the places of the keep lowest internal indices; they stay nearest first
+    std::vector<int> at(n);
+    for (int e = 0; e < n; ++e) at[e] = e;
+    std::sort(at.begin(), at.end(), [&](int x, int y) { return rec[x].j < rec[y].j; });
+    at.resize(keep);
+    std::sort(at.begin(), at.end());
+    // the kept entries of a row of n, then their block offsets, to the front
+    auto shorten = [&](void *row, size_t bytes, size_t offsets) {
+        const size_t entry = bytes + offsets;
+        std::vector<char> all(entry * n), kept(entry * keep);
+        if (hipMemcpy(all.data(), row, all.size(), hipMemcpyDeviceToHost) != hipSuccess) return false;
+        for (int e = 0; e < keep; ++e) {
+            std::memcpy(&kept[bytes * e], &all[bytes * at[e]], bytes);
+            std::memcpy(kept.data() + bytes * keep + offsets * e, all.data() + bytes * n + offsets * at[e], offsets);
+        }
+        return kept.empty() || hipMemcpy(row, kept.data(), kept.size(), hipMemcpyHostToDevice) == hipSuccess;
+    };
+    int32_t bo = block_of(rw, i), bo64 = 0, len = 0;
+    if ((g.blk_off && hipMemcpy(&bo, g.blk_off + i, sizeof(bo), hipMemcpyDeviceToHost) != hipSuccess) ||
+        hipMemcpy(&bo64, g.blk64_off + i, sizeof(bo64), hipMemcpyDeviceToHost) != hipSuccess)
+        return VOR_EDEVICE;
+    BlockHdr *h = reinterpret_cast<BlockHdr *>(g.blk + bo), *h64 = reinterpret_cast<BlockHdr *>(g.blk64 + bo64);
+    if (!shorten(g.rec64 + rw.x, sizeof(Rec64), 0) ||
+        !shorten(g.blk + bo + kHdrSlots, g.compact ? 8 : 12, sizeof(int32_t)) ||
+        !shorten(g.blk64 + bo64 + kHdrSlots, 24, sizeof(int32_t)) ||
+        hipMemcpy(&len, &h->len, sizeof(len), hipMemcpyDeviceToHost) != hipSuccess)
+        return VOR_EDEVICE;
+    len = (len & ~kLenMask) | keep;   // the scale exponent stays
+    rw.y = keep;
+    if (hipMemcpy(g.rows + i, &rw, sizeof(rw), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(&h->len, &len, sizeof(len), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(&h64->len, &keep, sizeof(keep), hipMemcpyHostToDevice) != hipSuccess)
+        return VOR_EDEVICE;
     return VOR_OK;
 }
 
