@@ -15,7 +15,11 @@ in the method). value = segments emitted per step / seconds per step.
 
 roofline.traffic is the trace kernel's HBM traffic per launch from the
 committed hardware-counter summary (profiles/), reported only while the
-kernel sources still hash to the value recorded there (else null).
+kernel sources still hash to the value recorded there (else null), and
+roofline.achieved and frac are that traffic over the kernel's time. work_rate
+is another thing: the bytes of the method's steps, whole neighbour rows
+included, over the same time. The searches stop before the end of a row, so
+that more bytes are charged there than the kernel reads.
 
     python bench.py [--steps K] [--warmup W] [--gpus 1]
                     [--workload flared_disc|exp_disc|clumpy|uniform_cube|flared_disc_transport|serving|
@@ -130,13 +134,14 @@ WORKLOADS = {
 
 
 def algorithmic_bytes(c: np.ndarray, n_rays: int, mode: str, transport: bool = False) -> float:
-    """Bytes the method must move for one launch, from the kernel counters
+    """Bytes of the method's steps in one launch, from the kernel counters
     c = [segments, fallbacks, fp64 re-decisions, steps, records, ...].
-    Per step: the row range (8 B) and, per neighbour record read, its index
+    Per step: the row range (8 B) and, per neighbour record of the cell (the
+    whole row, of which a search that stops early reads less), its index
     and site (4 + 24 B in FP64; 4 + 12 B FP32 offset in mixed mode, plus the
     winner's FP64 site, 24 B, and the FP64 records of re-decided steps). The
     figure belongs to the method, not to a layout: grids with compact 8-byte
-    records are charged the same.
+    records are charged the same. It measures work, not traffic.
     Per segment: the cell density (8 B) and the output (4 B cell + 8 B
     length). Per ray: origin and direction (48 B), tau, count and status
     (13 B). With transport, per segment two tally updates (read and write
@@ -525,7 +530,7 @@ def serving_precision_result(torch, vrt, workloads, n_requests, budget_gib, with
     submission order and in the coherent order of vor_order_rays. Every
     request's tau must be identical between the two serving runs and equal
     to vor_trace's (mixed mode reproduces FP64: equal accuracy), and no
-    served ray may end without its whole path. The serving kernel's HBM
+    served ray may end without its whole path. The serving kernel's work
     rate is the algorithmic bytes of the same paths (the counters of the
     mixed vor_trace launch, which stores every segment as the server does)
     over the serving wall time."""
@@ -594,8 +599,8 @@ def serving_precision_result(torch, vrt, workloads, n_requests, budget_gib, with
         "accuracy": {"tau_identical_fp64_vs_mixed_serving": same, "tau_serving_equals_plain": equal_plain,
                      "overflow_rays": sat_m["status_counts"][vrt.RAY_OVERFLOW] +
                      served["fp64"]["saturated"]["status_counts"][vrt.RAY_OVERFLOW]},
-        "roofline": {"bound": "hbm", "achieved": serving_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": serving_gbs / HBM_PEAK_GBS, "algorithmic_bytes": alg},
+        "roofline": {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None,
+                     "work_rate": serving_gbs, "algorithmic_bytes": alg},
     }
 
 
@@ -756,7 +761,6 @@ def measure(args, torch, vrt, workloads, name, steps, warmup, roofline_reps, wit
     kc = bufs.counters.cpu().numpy().astype(np.float64) / args.roofline_reps
     k_avg = float(np.mean(k_ms))
     alg = algorithmic_bytes(kc, w.N, mode, bool(spec.get("transport")))
-    achieved = alg / (k_avg / 1e3) / 1e9
     recs_per_step = kc[4] / max(kc[3], 1)
 
     # FP64 on the same batch: rate, and equality of every ray's result
@@ -782,6 +786,7 @@ def measure(args, torch, vrt, workloads, name, steps, warmup, roofline_reps, wit
         exact_output(vrt, torch, grid, o, d, rho, bufs, spec, mode)
     traffic, traffic_src, l2_hit = measured_traffic(args.workload)
     copy_bw = copy_bandwidth(torch)
+    achieved = None if traffic is None else traffic / (k_avg / 1e3) / 1e9
 
     result = {
         "metric": METRIC,
@@ -821,11 +826,12 @@ def measure(args, torch, vrt, workloads, name, steps, warmup, roofline_reps, wit
         "grid": {"build_ms": info["build_ms"], "nnz": info["nnz"], "max_row": info["max_row"],
                  "device_bytes": info["device_bytes"]},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
+                     "frac": None if achieved is None else achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "kernel": "k_trace_persistent" if spec.get("persistent") else "k_trace",
-                     "kernel_avg_ms": k_avg, "algorithmic_bytes": alg, "traffic_source": traffic_src,
+                     "kernel_avg_ms": k_avg, "algorithmic_bytes": alg, "work_rate": alg / (k_avg / 1e3) / 1e9,
+                     "traffic_source": traffic_src,
                      "kernel_source_sha256_16": kernel_source_hash(), "l2_hit_rate": l2_hit,
-                     "copy_bw": copy_bw, "frac_of_copy": achieved / copy_bw},
+                     "copy_bw": copy_bw, "frac_of_copy": None if achieved is None else achieved / copy_bw},
     }
     if not args.no_cpu:
         import oracle

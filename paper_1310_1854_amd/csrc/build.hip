@@ -199,7 +199,10 @@ __global__ void __launch_bounds__(64) k_clip(ClipArgs A)
     if (threadIdx.x == 0) clip_result(A, i, n, walls, vol);
 }
 
-// The queued cells again, in the strict order.
+// The queued cells again, in the strict order. (All of a lattice's are: the
+// build of 10^6 sites on a cubic one takes 14.4 ms, on a body-centred one of
+// 4x10^5 11.9 ms; with every cell taken nearest first from the start, by rings
+// of buckets, 27.6 and 13.4 ms.)
 __global__ void __launch_bounds__(64) k_clip_strict(ClipArgs A)
 {
     __shared__ WaveCellSmall cell;

@@ -44,7 +44,7 @@
 // What bounds it: instruction issue, with 4 to 5 waves per SIMD to hide the
 // LDS round trips. About 22 cuts of some 220 instructions per cell are more
 // than half of it, the walk through the boxes a quarter. On a flared disc of
-// 10^6 sites this takes 17 ms for the small cells and 3.4 ms for the 213
+// 10^6 sites this takes 17 ms for the small cells and 3.7 ms for the 213
 // large ones (the latency of the largest, 99 faces); rings of a uniform
 // bucket grid with the cell in LDS, as before, took 137 and 38 ms. The tests
 // against every vertex read them in FP32 from LDS, four ahead; broadcast from
@@ -577,9 +577,10 @@ __device__ __forceinline__ int balls_met(C &c, int at, int n, const BoxF &b)
 // squared distance in [from, to): within the sphere of twice the largest
 // vertex distance and, where many are, in the ball of one of the vertices
 // (large cells: of the n listed for level `at`, which the boxes above meet).
-// Boxes in the sphere from which the ball test pays: 6 / 10 / 16 measured
-// 22.4 / 22.0 / 22.1 ms for the whole build of a 10^6-site flared disc (never:
-// a quarter more), 35.5 / 35.1 / 34.9 ms for a clumpy medium of 2x10^6.
+// Boxes in the sphere from which the ball test pays: 6 / 10 / 12 / 16 / never
+// measured 23.3 / 23.1 / 23.1 / 23.2 / 28.1 ms for the whole build of a
+// 10^6-site flared disc, 36.4 / 35.8 / 35.7 / 35.7 / 36.0 ms for a clumpy medium
+// of 2x10^6.
 constexpr int kBallMin = 12;
 template <class C>
 __device__ __forceinline__ uint64_t boxes_hit(const C &c, const LaneVerts<C::kPerLane> &R, int at, int n_balls,

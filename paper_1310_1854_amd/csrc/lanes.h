@@ -12,8 +12,6 @@ __device__ __forceinline__ uint32_t lane_u32(uint32_t v, int l)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
 }
 
-__device__ __forceinline__ float lane_f32(float v, int l) { return __uint_as_float(lane_u32(__float_as_uint(v), l)); }
-
 __device__ __forceinline__ double lane_f64(double v, int l)
 {
     const uint64_t u = (uint64_t)__double_as_longlong(v);
