@@ -148,7 +148,7 @@ struct ClipArgs {
     uint8_t *walls;           // [M]
     int32_t *retry;           // [M] sites whose cell needs the large capacity
     int32_t *n_retry;
-    int32_t *touched;         // [M] sites whose cell goes to the strict order
+    int32_t *touched;         // [M] sites whose cell goes to the strict order; null: every one
     int32_t *n_touched;
     int32_t *open;            // [M] sites whose cell came out of the strict order as no polyhedron
     int32_t *n_open;
@@ -199,14 +199,15 @@ __global__ void __launch_bounds__(64) k_clip(ClipArgs A)
     if (threadIdx.x == 0) clip_result(A, i, n, walls, vol);
 }
 
-// The queued cells again, in the strict order. (All of a lattice's are: the
+// The queued cells again, in the strict order; up to 64 sites, every cell (the
+// loose order's head start would be all of them). (All of a lattice's are: the
 // build of 10^6 sites on a cubic one takes 14.4 ms, on a body-centred one of
 // 4x10^5 11.9 ms; with every cell taken nearest first from the start, by rings
 // of buckets, 27.6 and 13.4 ms.)
 __global__ void __launch_bounds__(64) k_clip_strict(ClipArgs A)
 {
     __shared__ WaveCellSmall cell;
-    const int64_t i = A.touched[blockIdx.x];
+    const int64_t i = A.touched ? A.touched[blockIdx.x] : (int)blockIdx.x;
     uint32_t walls = 0;
     double vol = 0.0;
     int n = wclip_site<WaveCellSmall, true>(cell, A.sites, A.M, A.tree, A.box, i, A.nbr + i * kMaxNbr, kMaxNbr, walls, vol,
@@ -881,7 +882,12 @@ extern "C" vor_status vor_build_grid(const double *sites, int64_t M, const doubl
     ca.volume = g.volume;
     ca.bbox = g.bbox;
     if (hipMemsetAsync(slot, 0xff, sizeof(int32_t) * M, st) != hipSuccess) return fail(VOR_EDEVICE);
-    hipLaunchKernelGGL(k_clip, dim3((unsigned)(kXcds * ((M + kXcds - 1) / kXcds))), dim3(64), 0, st, ca);
+    if (M <= 64) {
+        ca.touched = nullptr;
+        hipLaunchKernelGGL(k_clip_strict, dim3((unsigned)M), dim3(64), 0, st, ca);
+    } else {
+        hipLaunchKernelGGL(k_clip, dim3((unsigned)(kXcds * ((M + kXcds - 1) / kXcds))), dim3(64), 0, st, ca);
+    }
     if (hipGetLastError() != hipSuccess) return fail(VOR_EDEVICE);
     int hflags[7] = {0, 0, 0, 0, 0, 0, 0};
     auto clipped = [&]() {   // the counts so far, or why the build has failed

@@ -123,7 +123,6 @@ struct LaneVerts {
     double sc;              // wave-uniform: a power of two that scales the box to about 1, for FP32
     int np;                 // wave-uniform: plane slots in use
     double tol;             // wave-uniform: relative tolerance of the cuts
-    bool loose;             // wave-uniform: the planes do not come strictly nearest first
 };
 
 __device__ __forceinline__ uint32_t wpack3(int a, int b, int c)
@@ -297,9 +296,9 @@ __device__ __forceinline__ void wcell_init(C &c, LaneVerts<C::kPerLane> &R, cons
 }
 
 // Cut the cell by {v : n.v <= d} (plane id `id`, all wave-uniform). Returns
-// 1, 0 when the plane cuts nothing off, or an -ERR_* code: in the loose order
+// 1, 0 when the plane cuts nothing off, or an -ERR_* code: unless STRICT
 // ERR_TOUCH when the cut passes through a vertex, to within its tolerance.
-template <class C>
+template <bool STRICT, class C>
 __device__ __forceinline__ int wcell_cut(C &c, LaneVerts<C::kPerLane> &R, double nx, double ny, double nz, double d,
                                          int32_t id)
 {
@@ -318,7 +317,7 @@ __device__ __forceinline__ int wcell_cut(C &c, LaneVerts<C::kPerLane> &R, double
         kept |= R.valid[q] & ~off[q];
     }
     if (any == 0) return 0;
-    if (R.loose && on != 0) return -ERR_TOUCH;
+    if (!STRICT && on != 0) return -ERR_TOUCH;
     if (kept == 0) return -ERR_DEGENERATE;   // the site itself is always strictly inside
     // plane slot of the new face: a fresh one, or one no kept vertex uses
     int Pn = R.np;
@@ -492,7 +491,7 @@ __device__ __forceinline__ int wcell_take(C &c, LaneVerts<C::kPerLane> &R, doubl
         }
         const int w = __ffsll((long long)first) - 1;
         const double dd = 0.5 * lane_f64(d2, w);
-        const int rc = wcell_cut(c, R, lane_f64(nx, w), lane_f64(ny, w), lane_f64(nz, w), dd, (int32_t)lane_u32((uint32_t)j, w));
+        const int rc = wcell_cut<STRICT>(c, R, lane_f64(nx, w), lane_f64(ny, w), lane_f64(nz, w), dd, (int32_t)lane_u32((uint32_t)j, w));
         if (rc < 0) return rc;
         act = act && lane_id() != w;
         tested = tested && rc == 0;
@@ -820,8 +819,8 @@ __device__ __forceinline__ void wcell_bbox(const LaneVerts<K> &R, const double p
 // mask and the volume go to the caller's variables. Returns the count or
 // -ERR_*. All lanes of the wave call it with the same i. STRICT takes every
 // site nearest first, without the Hilbert neighbourhood's head start;
-// otherwise (with more than 64 sites) the order is loose, and a cell in which
-// a cut passes through a vertex is refused with ERR_TOUCH. tol is the relative
+// otherwise the order is loose, and a cell in which a cut passes through a
+// vertex is refused with ERR_TOUCH. tol is the relative
 // tolerance of the cuts; a cell that is no closed polyhedron at the end is
 // refused with ERR_OPEN unless `open` lets it pass.
 template <class C, bool STRICT>
@@ -838,7 +837,6 @@ __device__ __forceinline__ int wclip_site(C &c, const Site *__restrict__ sites, 
     for (int a = 0; a < 3; ++a) slack = fmax(slack, 1e-15 * fmax(fabs(box.lo[a]), fabs(box.hi[a])));
     LaneVerts<K> R;
     R.tol = tol;
-    R.loose = !STRICT && M > 64;
     wcell_init(c, R, p, box);
     // the nearer half of the neighbourhood in Hilbert order (of up to 64 sites: everything)
     const int64_t w0 = max((int64_t)0, min(i - 32, M - 64));

@@ -103,8 +103,17 @@ def _rounded_points(seed):
     return s + r.normal(size=s.shape) * 10 ** r.uniform(-16, -11)
 
 
+def _few(seed):
+    """At most 64 sites: all of a cell's planes come at once."""
+    r = np.random.default_rng(seed)
+    n = int(r.integers(8, 33))
+    s = np.unique(r.integers(-3, 4, (2 * n, 3)) / 3.5, axis=0)
+    return s + r.normal(size=s.shape) * 10 ** r.uniform(-16, -9)
+
+
 # Cells that need their planes in the exact order of distance: planes of a far cluster's sites, nearly parallel, at
 # distances equal to 2^-20; lattice points with distances equal to the disturbance of their coordinates.
-@pytest.mark.parametrize("sites,seed", [(_far_cluster, 2349), (_rounded_points, 2012), (_rounded_points, 4604)])
+@pytest.mark.parametrize("sites,seed", [(_far_cluster, 2349), (_rounded_points, 2012), (_rounded_points, 4604),
+                                        (_few, 206), (_few, 3378)])
 def test_planes_come_in_the_exact_order(vrt, sites, seed):
     _check(vrt, sites(seed))
