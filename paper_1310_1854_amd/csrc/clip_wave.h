@@ -491,7 +491,8 @@ __device__ __forceinline__ int wcell_take(C &c, LaneVerts<C::kPerLane> &R, doubl
         }
         const int w = __ffsll((long long)first) - 1;
         const double dd = 0.5 * lane_f64(d2, w);
-        const int rc = wcell_cut<STRICT>(c, R, lane_f64(nx, w), lane_f64(ny, w), lane_f64(nz, w), dd, (int32_t)lane_u32((uint32_t)j, w));
+        const int rc = wcell_cut<STRICT>(c, R, lane_f64(nx, w), lane_f64(ny, w), lane_f64(nz, w), dd,
+                                         (int32_t)lane_u32((uint32_t)j, w));
         if (rc < 0) return rc;
         act = act && lane_id() != w;
         tested = tested && rc == 0;

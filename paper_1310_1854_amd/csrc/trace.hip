@@ -365,7 +365,8 @@ __global__ void __launch_bounds__(256) k_trace_group(TraceArgs A)
                 if (A.start && li == 0) A.start[ray] = m;
             }
             R.s_c = s0;
-            group_walk<MODE, SEGS, EXT, false, W>(A.G, A.I, A.O, A.X, R, S, m, EXT && A.N >= GroupTally::kMinRays ? &tally : nullptr);
+            group_walk<MODE, SEGS, EXT, false, W>(A.G, A.I, A.O, A.X, R, S, m,
+                                                  EXT && A.N >= GroupTally::kMinRays ? &tally : nullptr);
         } else {
             R.L = 0.0;
             if (EXT) ray_extras_begin(A.X, ray, R);
@@ -395,7 +396,8 @@ __global__ void __launch_bounds__(256) k_trace_group(TraceArgs A)
     if (__shfl(at, 0, 64) == 3) {   // the block's last wave
         if (tallies) tally_flush(A.X, tally);
         const int i = threadIdx.x & 63;
-        const unsigned long long v = A.counters && i < 7 ? __hip_atomic_load(&sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0ull;
+        unsigned long long v = 0;
+        if (A.counters && i < 7) v = __hip_atomic_load(&sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (v) atomicAdd(&A.counters[i], v);
     }
 }
