@@ -41,10 +41,10 @@
 // a simple polyhedron) show that at the end, and the cell is clipped again
 // with another tolerance: see strict_site.
 //
-// What bounds it: instruction issue, with 4 to 5 waves per SIMD to hide the
+// What bounds it: vector issue (98% busy), with 4 waves per SIMD to hide the
 // LDS round trips. About 22 cuts of some 220 instructions per cell are more
 // than half of it, the walk through the boxes a quarter. On a flared disc of
-// 10^6 sites this takes 17 ms for the small cells and 3.7 ms for the 213
+// 10^6 sites this takes 17.3 ms for the small cells and 3.4 ms for the 213
 // large ones (the latency of the largest, 99 faces); rings of a uniform
 // bucket grid with the cell in LDS, as before, took 137 and 38 ms. The tests
 // against every vertex read them in FP32 from LDS, four ahead; broadcast from
